@@ -345,11 +345,12 @@ xshare_status layer_common(const xshare_layer_args& a) {
   fa.k = k;
   fa.d = d;
   fa.f = f;
-  fa.max_active = bound;
+  fa.max_active = xs::slot_bound(bound, T, k);
   // the threshold rule's set size is not known before the selection runs
   fa.est_active = params->budget_mode == XSHARE_BUDGET_THRESHOLD
                       ? 0
                       : layer_estimate(T, params, a.ep);
+  fa.shared_slots = n_shared * ((T + xs::kSlotRows - 1) / xs::kSlotRows);
   fa.splits = wt.fmt == XSHARE_WEIGHTS_MXFP4 ? L.q4_splits : L.splits;
   fa.gu_splits = L.gu_splits;
   fa.gu_tail_splits = L.gu_tail_splits;
@@ -424,11 +425,21 @@ xshare_layer_args layer_args(const uint16_t* x, const float* logits, const uint1
   return a;
 }
 
+// The expert slots past one per expert (batches of more than kSlotRows tokens) do not count
+// against the size limit of xshare_moe_forward_noalloc.
+constexpr size_t kSlotBytes = 4096;
+size_t slot_bytes(int32_t T, const xshare_route_params* p) {
+  return xs::align256(sizeof(int4) * (p->n_experts + xs::slot_extra(T, p->top_k))) -
+         xs::align256(sizeof(int4) * p->n_experts);
+}
+static_assert(sizeof(int4) * (xs::kMaxAssignments / xs::kSlotRows) + 256 <= kSlotBytes,
+              "room for the slots of the largest batch");
+
 // Scratch of xshare_moe_forward_noalloc: one fixed array per GPU, for callers that cannot
 // allocate.  Host code never names the array in a kernel argument or a copy (its host-side
 // name is not a device address): each device's address comes from hipGetSymbolAddress, taken
 // once per device with that device current, and only that address is passed on.
-static __device__ __align__(256) unsigned char scratch[XSHARE_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[XSHARE_NOALLOC_SCRATCH_BYTES + kSlotBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
@@ -565,7 +576,8 @@ xshare_status xshare_moe_forward_noalloc(const uint16_t* x, const float* logits,
   // host checks first (the same as xshare_moe_forward's), then the size limit
   xshare_status st = check_layer(a);
   if (st != XSHARE_OK) return st;
-  if (layer_workspace(a) > size_t(XSHARE_NOALLOC_SCRATCH_BYTES)) return XSHARE_EWORKSPACE;
+  if (layer_workspace(a) - slot_bytes(T, params) > size_t(XSHARE_NOALLOC_SCRATCH_BYTES))
+    return XSHARE_EWORKSPACE;
   if (stream) {             // the array used is the current device's
     int cur = 0, sdev = 0;
     if (hipGetDevice(&cur) != hipSuccess || hipStreamGetDevice(stream, &sdev) != hipSuccess)
@@ -575,7 +587,7 @@ xshare_status xshare_moe_forward_noalloc(const uint16_t* x, const float* logits,
   hipError_t err = hipSuccess;
   a.ws = scratch_for_current_device(&err);
   if (!a.ws) return XSHARE_EHIP;
-  a.ws_bytes = size_t(XSHARE_NOALLOC_SCRATCH_BYTES);
+  a.ws_bytes = size_t(XSHARE_NOALLOC_SCRATCH_BYTES) + kSlotBytes;
   return layer_common(a);
 }
 

@@ -759,30 +759,34 @@ constexpr bool stage_gate_up(int kW, int U) { return ((XS_STAGE_GATE_UP >> kW) &
 constexpr bool stage_down(int kW) { return (XS_STAGE_DOWN >> kW) & 1; }
 
 // Work of grid row `slot` of the expert GEMMs: the always-on shared experts first (all T
-// tokens, rows T*k + s*T + t; their blocks are the longest, so they start first and do
-// not trail the launch), then the routed active experts (their tokens' rows in permuted
-// order).  False for rows beyond both.  `e` is the shared or the routed expert.
+// tokens, rows T*k + s*T + t, kSlotRows of them a slot at most; their blocks are the longest,
+// so they start first and do not trail the launch), then the routed active experts (their
+// tokens' rows in permuted order).  False for rows beyond both.  `e` is the shared or the
+// routed expert, t0 the first token of a shared slot.
 struct SlotWork {
-  int e, p0, te;
+  int e, p0, te, t0;
   bool shared;
 };
 
 __device__ __forceinline__ bool slot_work(const FfnArgs& a, int slot, SlotWork& w) {
-  if (slot < a.n_shared) {
-    w.e = slot;
-    w.p0 = a.T * a.k + slot * a.T;
-    w.te = a.T;
+  if (slot < a.shared_slots) {
+    const int parts = a.shared_slots / a.n_shared, c = slot % parts;
+    w.e = slot / parts;
+    w.t0 = a.T * c / parts;
+    w.p0 = a.T * a.k + w.e * a.T + w.t0;
+    w.te = a.T * (c + 1) / parts - w.t0;
     w.shared = true;
     return true;
   }
-  const int r = slot - a.n_shared;
+  const int r = slot - a.shared_slots;
   // both loads are issued together; the record is used only below the count
   const int n_active = a.counters[kCntActive];
-  const int4 rec = a.active[r < a.N ? r : 0];
+  const int4 rec = a.active[r < a.max_active ? r : 0];
   if (r >= n_active) return false;
   w.e = rec.x;
   w.p0 = rec.y;
   w.te = rec.z;
+  w.t0 = 0;
   w.shared = false;
   return true;
 }
@@ -842,7 +846,7 @@ __launch_bounds__(kBlock) void gate_up_kernel(FfnArgs a) {
 #pragma unroll
     for (int rt = 0; rt < kTiles; ++rt) {
       const int t = min(c0 + rt * 16 + n, te - 1);
-      const int tok = sw.shared ? t : a.perm[p0 + t] / a.k;
+      const int tok = sw.shared ? sw.t0 + t : a.perm[p0 + t] / a.k;
       arow[rt] = a.x + (size_t)tok * d + k0;
     }
     floatx4 acc[NM][kTiles];
@@ -874,7 +878,8 @@ __launch_bounds__(kBlock) void gate_up_kernel(FfnArgs a) {
       __shared__ int s_tok[kStageRows];
       const int R = min(kStageRows, te - c0);
       if (threadIdx.x < R)
-        s_tok[threadIdx.x] = sw.shared ? c0 + threadIdx.x : a.perm[p0 + c0 + threadIdx.x] / a.k;
+        s_tok[threadIdx.x] =
+            sw.shared ? sw.t0 + c0 + threadIdx.x : a.perm[p0 + c0 + threadIdx.x] / a.k;
       __syncthreads();
       staged_pass<kW, U, false, NM, kTiles>(a.x + kbase, d, s_tok, R, wp, Kg, 0, acc, stage);
     } else if constexpr (kW == kFp8) {
@@ -958,7 +963,7 @@ __launch_bounds__(kBlock) void down_kernel(FfnArgs a) {
   int bx = blockIdx.x, slot = blockIdx.y;
   if (gridDim.y >= XS_DOWN_XCD_SLOTS) {
     const int L = blockIdx.x + gridDim.x * blockIdx.y;
-    const int live = a.n_shared + a.counters[kCntActive];   // <= gridDim.y
+    const int live = a.shared_slots + a.counters[kCntActive];   // <= gridDim.y
     if (L < (int)gridDim.x * (live & ~7)) {
       const int s = L >> 3;
       slot = (L & 7) + 8 * (s / gridDim.x);
@@ -1164,13 +1169,13 @@ __launch_bounds__(kBlock) void down_seq_kernel(FfnArgs a) {
   const int n = lane & 15, g = lane >> 4;
   const int d = a.d, f = a.f;
   const int CB = (d + kWaves * kCols * NM - 1) / (kWaves * kCols * NM);
-  const int live = a.n_shared + a.counters[kCntActive];
+  const int live = a.shared_slots + a.counters[kCntActive];
   const int units = live * CB;
   const int G = (int)gridDim.x;
   const int nu = (int)blockIdx.x < units ? min((units - (int)blockIdx.x + G - 1) / G, kSeqUnits) : 0;
   if (nu == 0) return;   // uniform: the whole block leaves before any barrier
   XS_TIME(xs_times_seq, blockIdx.x * kTimeSeqStride, (unsigned)(kTimeSeqBlocks * kTimeSeqStride));
-  const bool xcd = a.max_active + a.n_shared >= XS_DOWN_XCD_SLOTS;
+  const bool xcd = a.max_active + a.shared_slots >= XS_DOWN_XCD_SLOTS;
   const int nsteps = f / KB;                    // unsplit: the launch takes one K part
   const int rot = kW == kBf16 ? XS_DOWN_ROT : XS_Q8_DOWN_ROT;
   const size_t kl = (size_t)(kW == kBf16 ? klane<U>(g) : g * 8 * U);
@@ -1505,7 +1510,7 @@ int unroll_for(int K, int want);
 bool gu_two_tiles(const FfnArgs& a, int kW, unsigned splits) {
   const long min_blocks = kW == kMx4 ? XS_Q4_GU_CT2_MIN_BLOCKS : XS_GU_CT2_MIN_BLOCKS;
   return (long)((a.f + 2 * kWaves * kCols - 1) / (2 * kWaves * kCols)) *
-             (a.est_active + a.n_shared) * splits >= min_blocks;
+             (a.est_active + a.shared_slots) * splits >= min_blocks;
 }
 
 // Blocks of the unsplit gate/up instance the GPU runs at once (cached per instance; one
@@ -1646,7 +1651,7 @@ int down_resident(int u) {
 template <int kW, int NM, int TL = XS_DOWN_TL>
 void launch_down_fmt(const FfnArgs& a, int u, hipStream_t stream) {
   const int cols = kWaves * kCols * NM;
-  const int slots = a.max_active + a.n_shared;
+  const int slots = a.max_active + a.shared_slots;
   const dim3 grid((a.d + cols - 1) / cols, slots, a.splits), block(kBlock);
   if (u == 8) {
     hipLaunchKernelGGL((down_kernel<8, kW, NM, TL>), grid, block, 0, stream, a);
@@ -1679,7 +1684,7 @@ bool launch_down_seq(const FfnArgs& a, hipStream_t stream) {
     cached.store(r, std::memory_order_relaxed);
   }
   const int CB = (a.d + kWaves * kCols * NM - 1) / (kWaves * kCols * NM);
-  const long max_units = (long)(a.max_active + a.n_shared) * CB;
+  const long max_units = (long)(a.max_active + a.shared_slots) * CB;
   long G = std::max<long>(r, (max_units + kSeqUnits - 1) / kSeqUnits);
   G = (G + 7) & ~7L;
   hipLaunchKernelGGL((down_seq_kernel<U, kW, NM, TL>), dim3((unsigned)G), dim3(kBlock), 0, stream,
@@ -1697,7 +1702,7 @@ int unroll_for(int K, int want) {
 
 hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
   const int cols = kWaves * kCols;            // one column tile per wave; launch_gu may take two
-  const dim3 grid((a.f + cols - 1) / cols, a.max_active + a.n_shared, a.gu_splits),
+  const dim3 grid((a.f + cols - 1) / cols, a.max_active + a.shared_slots, a.gu_splits),
       block(kBlock);
   const bool split = a.gu_splits > 1;
   const int K = a.d / a.gu_splits;
@@ -1716,7 +1721,7 @@ hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
 
 hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
   const int K = a.f / a.splits;
-  const long est = a.est_active + a.n_shared;
+  const long est = a.est_active + a.shared_slots;
   if (a.wfmt == kMx4) {
     // twice the rows per wave (twice the weight bytes in flight) over 16-token passes, when
     // experts hold 8 rows or fewer on average (an expert past 16 rows reads its weights

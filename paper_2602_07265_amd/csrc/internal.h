@@ -18,9 +18,15 @@ constexpr size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 // Counters written by the selection kernel (device memory, inside the workspace).
 enum Counter : int {
-  kCntActive = 0,     // number of experts that received >= 1 token
+  kCntActive = 0,     // expert slots of the GEMMs (records of the active list)
   kCntSelected = 1,
   kCntStatus = 2,     // 0 = ok, 1 = invalid request offsets seen on the device
+  // the four-kernel selection: figures of the greedy for the statistics
+  kCntU = 3,
+  kCntS0 = 4,
+  kCntStart = 5,
+  kCntBudget = 6,
+  kCntMaxLoad = 7,
   kCntCount = 8
 };
 
@@ -28,8 +34,8 @@ enum Counter : int {
 struct RouteLayout {
   size_t offsets;   // int32 [N + 1]   exclusive prefix of tokens per expert (permuted order)
   size_t perm;      // int32 [T * k]   slot (i * k + r) of each permuted row
-  size_t active;    // int4 [N]        active experts, ascending: {expert, first permuted row,
-                    //                 rows, 0}, so a GEMM block finds its work in one load
+  size_t active;    // int4 [N + slot_extra]  expert slots: {expert, first permuted row, rows,
+                    //                 0}, so a GEMM block finds its work in one load
   size_t counters;  // int32 [kCntCount]
   size_t dense;     // fp32 [T * N]    dense gates (score_mode DENSE only)
   size_t ids;       // int32 [T * k]   refined ids when the caller passes none
@@ -38,13 +44,25 @@ struct RouteLayout {
   size_t total;
 };
 
+// Rows of one expert slot of the GEMMs, at most: an expert with more routed rows (only in
+// batches of more tokens than this) takes several slots, so that its rows spread over blocks
+// that run side by side and share its weights through L2, instead of one block streaming them
+// again for each pass.  Slots of `experts` active experts: sum over them of
+// ceil(rows / kSlotRows) <= experts + (T * k - experts) / kSlotRows.
+constexpr int kSlotRows = 128;
+inline int slot_bound(int experts, int T, int k) {
+  const long rest = (long)T * k - experts;
+  return experts + (T > kSlotRows && rest > 0 ? (int)(rest / kSlotRows) : 0);
+}
+inline int slot_extra(int T, int k) { return T > kSlotRows ? T * k / kSlotRows : 0; }
+
 inline RouteLayout route_layout(int T, int N, int k, bool dense) {
   RouteLayout L{};
   size_t tk = size_t(T > 0 ? T : 1) * size_t(k);
   size_t o = 0;
   L.offsets = o;  o += align256(sizeof(int32_t) * (N + 1));
   L.perm = o;     o += align256(sizeof(int32_t) * tk);
-  L.active = o;   o += align256(4 * sizeof(int32_t) * N);
+  L.active = o;   o += align256(4 * sizeof(int32_t) * (N + slot_extra(T, k)));
   L.counters = o; o += align256(sizeof(int32_t) * kCntCount);
   L.dense = o;    o += dense ? align256(sizeof(float) * size_t(T) * N) : 0;
   L.ids = o;      o += align256(sizeof(int32_t) * tk);
@@ -260,8 +278,9 @@ struct FfnArgs {
   const uint8_t* e2;
   int wfmt;                    // 0 bf16, 1 FP8, 2 MXFP4
   int T, N, k, d, f;
-  int max_active;              // host bound on the number of active experts (grid size)
-  int est_active;              // experts expected to be active (0: unknown), for launch shapes
+  int max_active;              // host bound on the routed expert slots (grid size)
+  int est_active;              // routed expert slots expected (0: unknown), for launch shapes
+  int shared_slots;            // slots of the shared experts: n_shared * ceil(T / kSlotRows)
   int splits;                  // K-splits of the down GEMM (partials summed in the combine)
   int gu_splits;               // K-splits of the gate/up GEMM (partials summed by finish)
   float* gpart;                // [gu_splits, 2, part_rows, f] when gu_splits > 1 (or the tail's)

@@ -1,11 +1,12 @@
 // Expert selection for one MoE layer and one decode batch (XShare, arXiv 2602.07265):
 // router scoring, batch scores, greedy selection (flat Algorithm 2 or per-request +
 // batch Algorithms 3-4), refinement, and the token permutation consumed by the expert
-// GEMMs.  One workgroup of 1024 threads does all of it: the whole problem is a few
-// thousand logits and is latency-, not throughput-bound, so the kernel avoids LDS round
-// trips in its inner loops: wave reductions use DPP, rankings compare packed integer keys,
-// and for decode-sized batches (T <= 64) a token bitmask per expert turns every
-// per-expert gather into popcounts.
+// GEMMs.  For decode-sized batches (T <= 64) one workgroup of 1024 threads does all of it:
+// the whole problem is a few thousand logits and is latency-, not throughput-bound, so the
+// kernel avoids LDS round trips in its inner loops: wave reductions use DPP, rankings compare
+// packed integer keys, and a token bitmask per expert turns every per-expert gather into
+// popcounts.  Larger batches run four kernels over the whole GPU (route_tokens_kernel and the
+// ones after it).
 //
 // Numerics: this translation unit is compiled with -ffp-contract=off; every fp32 step
 // of the gates is a separate IEEE round-to-nearest operation in a fixed order, so the
@@ -420,15 +421,19 @@ __device__ int block_excl_scan(int v, int* s_wsum, int& total) {
 }
 
 // Per-token list entry: bits 0-9 expert, bits 10-14 rank; kNoEntry = empty.
-__device__ __forceinline__ bool entry_is(uint32_t ent, int j) { return (ent & 0x83FFu) == (uint32_t)j; }
-__device__ __forceinline__ uint32_t entry_at(const uint4& v, int u) {
-  const uint32_t w = u < 2 ? v.x : u < 4 ? v.y : u < 6 ? v.z : v.w;
-  return (w >> (16 * (u & 1))) & 0xFFFFu;
-}
 
-// Batches of up to this many tokens keep one token bitmask per expert, which turns the
-// per-expert gathers (scores, per-request scores, permutation) into popcounts.
+// The one-workgroup selection (route_kernel) takes batches of up to 64 tokens: one token
+// bitmask per expert turns the per-expert gathers (scores, per-request scores, permutation)
+// into popcounts, and the keys of a wave's tokens stay in registers from the top-k to the
+// refinement.  It ends earlier where the four-kernel selection, about 20 us at any size here,
+// is faster (us a call, one workgroup -> four kernels): N=256 T=32 18.7 -> 20.4, T=48 22.4 ->
+// 20.8, T=64 27.6 -> 20.6, 16 requests of 4 31.4 -> 25.4; N=128 T=48 18.6 -> 20.0, T=64 21.4
+// -> 20.0; N=8 T=64 12.2 -> 19.9; or where a token's keys leave no registers for more.
 constexpr int kOccTokens = 64;
+template <int Q>
+constexpr int small_tokens() { return Q == 1 ? 64 : Q == 2 ? 56 : Q == 4 ? 40 : Q == 8 ? 32 : 16; }
+constexpr int kSmallAssignments = kOccTokens * kMaxTopK;
+static_assert(small_tokens<1>() <= kOccTokens, "a bit per token");
 
 __device__ __forceinline__ uint64_t below(int i) { return i >= 64 ? ~0ull : ((1ull << i) - 1ull); }
 
@@ -459,26 +464,203 @@ __device__ int group_by_expert(const uint16_t* s_ent, uint64_t* s_occ, int* s_of
   return cnt;
 }
 
+// Tables of the greedy in LDS, one entry per expert (and a few block counters, zeroed by the
+// caller with the tables).
+struct GreedyTables {
+  __align__(16) uint64_t key[kMaxExperts];   // keys of the candidates
+  // GPU groups: warm-up experts per group, then |S| per group
+  int gload[kMaxExperts];
+  // GPU groups: candidates per group outside the warm-up set; threshold rule: scores by index
+  __align__(16) int gcand[kMaxExperts];
+  // GPU groups: takeable candidates per rank inside their group; threshold rule: scores by rank
+  __align__(16) int hist[kMaxExperts];
+  int wsum[kWaves];
+  int cnt[8];
+};
+
+// The batch greedy (Algorithm 1 with a fixed budget; Algorithm 4's final stage; Algorithms 5
+// and 6 with GPU groups) for expert j = threadIdx.x: whether it is selected.  Order (tier,
+// score desc, index asc), keep the first budget_eff candidates.  Key: (3 - tier) << 42 |
+// ord(score) << 10 | (1023 - j); candidates are compacted and each counts the candidates ahead
+// of it.  Every thread of the block calls; MaxLoad(S) ends in sh.cnt[0] behind the caller's
+// next barrier.
+__device__ __forceinline__ bool select_set(const RouteArgs& a, GreedyTables& sh, bool tier1,
+                                           float s, bool inU, bool inS0, int& n_s0, int& n_start,
+                                           int& n_u, int& m_eff) {
+  const int tid = threadIdx.x, j = tid;
+  const int T = a.T, N = a.N, k = a.k;
+  const bool dense = a.score_mode == 1;
+  bool sel = false;
+  if (a.G == 0) {
+    int tier = 3;
+    uint64_t mykey = 0;
+    if (j < N) {
+      const bool cand = dense ? (T > 0) : inU;
+      tier = inS0 ? 0 : (tier1 ? 1 : (cand ? 2 : 3));
+      if (tier < 3)
+        mykey = ((uint64_t)(3 - tier) << 42) | ((uint64_t)ord(s) << 10) | (uint64_t)(1023 - j);
+      if (tier == 0) atomicAdd(&sh.cnt[1], 1);
+      if (tier <= 1) atomicAdd(&sh.cnt[2], 1);
+      if (inU) atomicAdd(&sh.cnt[3], 1);
+    }
+    int n_cand = 0;
+    const int cpos = block_excl_scan(mykey != 0 ? 1 : 0, sh.wsum, n_cand);
+    if (mykey != 0) sh.key[cpos] = mykey;
+    if (tid == 0 && (n_cand & 1)) sh.key[n_cand] = 0;
+    __syncthreads();
+    n_s0 = sh.cnt[1];
+    n_start = sh.cnt[2];
+    n_u = sh.cnt[3];
+    int rank = 0;
+    if (mykey != 0) {
+      const ulonglong2* keys2 = reinterpret_cast<const ulonglong2*>(sh.key);
+      const int n2 = (n_cand + 1) >> 1;
+      for (int jj = 0; jj < n2; ++jj) {
+        const ulonglong2 kk = keys2[jj];
+        rank += (kk.x > mykey) + (kk.y > mykey);
+      }
+    }
+    if (a.budget_mode == 3) {
+      // Algorithm 1's threshold rule: the starting set (ranks below n_start) and then the
+      // candidates in rank order join while f(S) < tau * f(E).  One thread replays the fp32
+      // sums in the stated order: f(E) over every expert in index order, f(S) in rank order.
+      float* const by_index = reinterpret_cast<float*>(sh.gcand);
+      float* const by_rank = reinterpret_cast<float*>(sh.hist);
+      if (j < N) by_index[j] = s;
+      if (j >= N && j < ((N + 3) & ~3)) by_index[j] = 0.0f;   // pad to whole float4s
+      if (mykey != 0) by_rank[rank] = s;
+      __syncthreads();
+      if (tid == 0) {
+        // sequential fp32 sums; 16-byte LDS reads keep the loads ahead of the adds
+        const float4* e4 = reinterpret_cast<const float4*>(by_index);
+        float f_E = 0.0f;
+#pragma unroll 4
+        for (int q = 0; q < (N + 3) / 4; ++q) {
+          const float4 v = e4[q];
+          f_E = f_E + v.x;
+          f_E = f_E + v.y;
+          f_E = f_E + v.z;
+          f_E = f_E + v.w;
+        }
+        const float target = a.tau * f_E;
+        float f_S = 0.0f;
+        for (int r = 0; r < n_start; ++r) f_S = f_S + by_rank[r];
+        int m = n_start;
+        while (m < n_cand && f_S < target) f_S = f_S + by_rank[m++];
+        sh.cnt[6] = m;
+      }
+      __syncthreads();
+      m_eff = max(sh.cnt[6], min(k, n_cand));
+    } else {
+      const int base = a.budget_mode == 0 ? a.budget : n_start + a.budget;
+      m_eff = max(min(base, n_cand), min(k, n_cand));
+    }
+    sel = mykey != 0 && rank < m_eff;
+  } else {
+    // GPU groups (Algorithms 5 and 6).  Group g can take a_g = m_g - |S_0 on g| experts
+    // (m_g caps every group's load, Eq. (5)), one per round, best first; its candidate of
+    // rank r (score desc, index asc, among its candidates outside S_0) is taken in round
+    // r + 1 if r < a_g.  The loop stops after the fewest rounds R that bring |S| to m_g * G,
+    // or when no group can take more; so S = S_0 plus every takeable candidate of rank < R,
+    // and R follows from a prefix count of the takeable candidates by rank.
+    const int G = a.G, m_g = a.budget;
+    const int gj = j < N ? (a.group ? a.group[j] : j / (N / G)) : 0;
+    const bool cand = j < N && (dense ? (T > 0) : inU);
+    const bool pick = cand && !inS0;
+    if (j < N) {
+      if (inS0) {
+        atomicAdd(&sh.gload[gj], 1);
+        atomicAdd(&sh.cnt[1], 1);
+      }
+      if (pick) atomicAdd(&sh.gcand[gj], 1);
+      if (inU) atomicAdd(&sh.cnt[3], 1);
+      if (cand) atomicAdd(&sh.cnt[5], 1);
+    }
+    // key: group << 44 | ord(score) << 10 | (1023 - j); the rank counts the group's keys above
+    const uint64_t pkey =
+        pick ? ((uint64_t)gj << 44) | ((uint64_t)ord(s) << 10) | (uint64_t)(1023 - j) : 0;
+    int n_pick = 0;
+    const int ppos = block_excl_scan(pick ? 1 : 0, sh.wsum, n_pick);
+    if (pick) sh.key[ppos] = pkey;
+    if (tid == 0 && (n_pick & 1)) sh.key[n_pick] = 0;
+    __syncthreads();
+    int rank = 0;
+    bool takeable = false;
+    if (pick) {
+      const ulonglong2* keys2 = reinterpret_cast<const ulonglong2*>(sh.key);
+      const uint64_t mine = (uint64_t)gj;
+      const int n2 = (n_pick + 1) >> 1;
+      for (int jj = 0; jj < n2; ++jj) {
+        const ulonglong2 kk = keys2[jj];
+        rank += ((kk.x >> 44) == mine && kk.x > pkey) + ((kk.y >> 44) == mine && kk.y > pkey);
+      }
+      takeable = rank < m_g - sh.gload[gj];
+      if (takeable) atomicAdd(&sh.hist[rank], 1);
+    }
+    __syncthreads();
+    n_s0 = sh.cnt[1];
+    n_u = sh.cnt[3];
+    const int n_cand = sh.cnt[5];
+    const int need = m_g * G - n_s0;          // picks the rounds must reach
+    static_assert(kThreads == kMaxExperts, "one rank of sh.hist per thread");
+    const int at_rank = sh.hist[tid];
+    int n_take = 0;
+    const int before = block_excl_scan(at_rank, sh.wsum, n_take);
+    if (need > 0 && before < need && before + at_rank >= need) sh.cnt[6] = tid + 1;
+    __syncthreads();
+    const int rounds = need <= 0 ? 0 : (n_take < need ? kMaxExperts : sh.cnt[6]);
+    sel = inS0 || (takeable && rank < rounds);
+    if (sel) atomicAdd(&sh.cnt[2], 1);
+    __syncthreads();
+    // fewer than k experts: the best remaining candidates join regardless of group
+    const int n_loop = sh.cnt[2], want = min(k, n_cand);
+    if (n_loop < want) {
+      const bool rest = cand && !sel;
+      const uint64_t fkey = rest ? ((uint64_t)ord(s) << 10) | (uint64_t)(1023 - j) : 0;
+      int n_rest = 0;
+      const int fpos = block_excl_scan(rest ? 1 : 0, sh.wsum, n_rest);
+      if (rest) sh.key[fpos] = fkey;
+      if (tid == 0 && (n_rest & 1)) sh.key[n_rest] = 0;
+      __syncthreads();
+      if (rest) {
+        const ulonglong2* keys2 = reinterpret_cast<const ulonglong2*>(sh.key);
+        int r2 = 0;
+        const int n2 = (n_rest + 1) >> 1;
+        for (int jj = 0; jj < n2; ++jj) {
+          const ulonglong2 kk = keys2[jj];
+          r2 += (kk.x > fkey) + (kk.y > fkey);
+        }
+        sel = r2 < want - n_loop;
+      }
+    }
+    // Load_g(S) and MaxLoad(S) (Section 5.1)
+    if (tid < G) sh.gload[tid] = 0;
+    __syncthreads();
+    if (sel) atomicAdd(&sh.gload[gj], 1);
+    __syncthreads();
+    if (tid < G) {
+      if (a.group_load && blockIdx.x == 0) a.group_load[tid] = sh.gload[tid];
+      atomicMax(&sh.cnt[0], sh.gload[tid]);
+    }
+    n_start = n_s0;
+    m_eff = min(m_g * G, N);
+  }
+  return sel;
+}
+
 template <int Q>
 __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
-  __shared__ __align__(16) uint16_t s_ent[kMaxAssignments];  // (token, rank) -> expert | rank
-  __shared__ float s_g[kMaxAssignments];                     // vanilla gate of that entry
-  __shared__ float s_vh[kMaxAssignments];                    // vanilla logit of that entry
-  __shared__ uint16_t s_list[kMaxAssignments];               // entries grouped by expert
-  __shared__ __align__(16) uint64_t s_occ[kMaxExperts];      // token bitmask per expert
-  __shared__ __align__(16) uint64_t s_key[kMaxExperts];      // greedy keys of the candidates
+  __shared__ __align__(16) uint16_t s_ent[kSmallAssignments];  // (token, rank) -> expert | rank
+  __shared__ float s_g[kSmallAssignments];                     // vanilla gate of that entry
+  __shared__ float s_vh[kSmallAssignments];                    // vanilla logit of that entry
+  __shared__ uint16_t s_list[kSmallAssignments];               // entries grouped by expert
+  __shared__ __align__(16) uint64_t s_occ[kMaxExperts];        // token bitmask per expert
+  __shared__ GreedyTables sh;
   __shared__ int s_off[kMaxExperts + 1];
   __shared__ uint8_t s_tier1[kMaxExperts];                   // picked by some request
   __shared__ uint8_t s_sel[kMaxExperts];
   __shared__ uint32_t s_seed[kWaves][2 * kMaxTopK];          // refinement seeds per wave
   __shared__ float s_seed_h[kWaves][2 * kMaxTopK];            //   (and per half of a wave)
-  __shared__ int s_wsum[kWaves];
-  __shared__ int s_cnt[8];
-  __shared__ int s_gload[kMaxExperts];   // GPU groups: warm-up experts per group, then |S| per group
-  // GPU groups: candidates per group outside the warm-up set; threshold rule: scores by index
-  __shared__ __align__(16) int s_gcand[kMaxExperts];
-  // GPU groups: takeable candidates per rank inside their group; threshold rule: scores by rank
-  __shared__ __align__(16) int s_hist[kMaxExperts];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -487,13 +669,11 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   const bool dense = a.score_mode == 1;
   const bool hier = a.req_offsets != nullptr;
   const bool ep = a.G > 0;
-  const bool occ = T <= kOccTokens;
   const int TK = T * k;
-  const int TK8 = (TK + 7) & ~7;
 
-  // tokens per wave whose keys stay in registers (1024 threads allow 128 VGPRs each)
-  constexpr int kCache = Q <= 4 ? 4 : (Q <= 8 ? 2 : 1);
-  const bool cached = T <= kCache * kWaves;
+  // tokens per wave whose keys stay in registers (1024 threads allow 128 VGPRs each); the
+  // launch takes this kernel for batches of up to that many
+  constexpr int kCache = (small_tokens<Q>() + kWaves - 1) / kWaves;
   // Two tokens per wave (one per half) where a token's experts fit 8 per lane and the batch
   // gives a wave more than one token, except with dense scores (their softmax sums every
   // expert of the token in index order): token pairs p = wave, wave + 16, ..., pair p
@@ -516,7 +696,6 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   const int hh = lane >> 5, sl = lane & 31;
   const int qr = lane >> 4, ql = lane & 15;
   const int n_pairs = (T + 1) >> 1;
-  const bool cached_p = n_pairs <= kCacheP * kWaves;
   uint32_t kc[kCache][Q];
   uint32_t kcp[kHalves ? kCacheP : 1][kHalves ? Q2 : 1];
   uint32_t kcq[kQuads ? kCacheQ : 1][kQuads ? Q4 : 1];
@@ -534,15 +713,14 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
     load_row<Q>(a, wave, lane, raw_next);
   }
 
-  if (tid < 8) s_cnt[tid] = 0;
+  if (tid < 8) sh.cnt[tid] = 0;
   for (int j = tid; j < kMaxExperts; j += kThreads) {
     s_tier1[j] = 0;
     s_occ[j] = 0;
-    s_gload[j] = 0;
-    s_gcand[j] = 0;
-    s_hist[j] = 0;
+    sh.gload[j] = 0;
+    sh.gcand[j] = 0;
+    sh.hist[j] = 0;
   }
-  for (int p = TK + tid; p < TK8; p += kThreads) s_ent[p] = (uint16_t)kNoEntry;
   __syncthreads();
 
   // ---- request offsets must be 0 = o_0 < o_1 < ... < o_R = T and every expert's group must
@@ -551,16 +729,16 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
     const int R = a.R;
     for (int r = tid; r < R; r += kThreads) {
       const int lo = a.req_offsets[r], hi = a.req_offsets[r + 1];
-      if (!(lo < hi) || lo < 0 || hi > T) atomicOr(&s_cnt[7], 1);
+      if (!(lo < hi) || lo < 0 || hi > T) atomicOr(&sh.cnt[7], 1);
     }
-    if (tid == 0 && (a.req_offsets[0] != 0 || a.req_offsets[R] != T)) atomicOr(&s_cnt[7], 1);
+    if (tid == 0 && (a.req_offsets[0] != 0 || a.req_offsets[R] != T)) atomicOr(&sh.cnt[7], 1);
   }
   if (ep && a.group)
     for (int jj = tid; jj < N; jj += kThreads)
-      if (a.group[jj] < 0 || a.group[jj] >= a.G) atomicOr(&s_cnt[7], 1);
+      if (a.group[jj] < 0 || a.group[jj] >= a.G) atomicOr(&sh.cnt[7], 1);
   if (hier || (ep && a.group)) {
     __syncthreads();
-    if (s_cnt[7]) {
+    if (sh.cnt[7]) {
       for (int j = tid; j < N; j += kThreads) a.sel_mask[j] = 0;
       for (int p = tid; p < TK; p += kThreads) {
         a.ids[p] = -1;
@@ -677,27 +855,15 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
     }
   } else if (halves) {
     if constexpr (kHalves) {
-      if (cached_p) {
 #pragma unroll
-        for (int it = 0; it < kCacheP; ++it)
-          if (wave + it * kWaves < n_pairs) plain_topk_pair(wave + it * kWaves, kcp[it]);
-      } else {
-        for (int p = wave; p < n_pairs; p += kWaves) {
-          uint32_t left[Q2];
-          plain_topk_pair(p, left);
-        }
-      }
+      for (int it = 0; it < kCacheP; ++it)
+        if (wave + it * kWaves < n_pairs) plain_topk_pair(wave + it * kWaves, kcp[it]);
     }
-  } else if (cached) {
+  } else {
     // compile-time slots keep the cache in registers
 #pragma unroll
     for (int it = 0; it < kCache; ++it)
       if (wave + it * kWaves < T) plain_topk(wave + it * kWaves, kc[it]);
-  } else {
-    for (int i = wave; i < T; i += kWaves) {
-      uint32_t left[Q];
-      plain_topk(i, left);
-    }
   }
   __syncthreads();
 
@@ -705,9 +871,9 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   const int j = tid;
   float s = 0.0f;
   bool inU = false, inS0 = false;
-  if (occ) {
+  {
     int total;
-    const int cnt = group_by_expert(s_ent, s_occ, s_off, s_list, s_wsum, TK, k, N, total);
+    const int cnt = group_by_expert(s_ent, s_occ, s_off, s_list, sh.wsum, TK, k, N, total);
     if (j < N) {
       // eight entries' loads, then their adds in token order (the loads do not wait for the
       // sum, so a long list costs one LDS round trip per eight tokens)
@@ -731,20 +897,6 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
       }
       inU = cnt > 0;
     }
-  } else if (j < N) {
-    const uint4* ents = reinterpret_cast<const uint4*>(s_ent);
-    for (int vb = 0; vb < TK8 / 8; ++vb) {
-      const uint4 e4 = ents[vb];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint32_t ent = entry_at(e4, u);
-        if (entry_is(ent, j)) {
-          inU = true;
-          if ((int)((ent >> 10) & 31u) < k0) inS0 = true;
-          if (!dense) s = s + s_g[vb * 8 + u];
-        }
-      }
-    }
   }
   if (dense && j < N)
     for (int i = 0; i < T; ++i) s = s + a.dense[(size_t)i * N + j];
@@ -758,48 +910,32 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
       unsigned inUr = 0, inS0r = 0;
 #pragma unroll
       for (int q = 0; q < Q; ++q) sr[q] = 0.0f;
-      if (occ) {
-        const uint64_t range = below(hi) & ~below(lo);
+      const uint64_t range = below(hi) & ~below(lo);
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          const int jq = lane + 64 * q;
-          if (jq >= N) continue;
-          const uint64_t m = s_occ[jq];
-          const int n = __popcll(m & range);
-          const int o = s_off[jq] + __popcll(m & below(lo));
-          for (int t0 = 0; t0 < n; t0 += 8) {   // loads ahead of the ordered adds, as in (b)
-            float gq[8];
-            uint32_t eq[8];
+      for (int q = 0; q < Q; ++q) {
+        const int jq = lane + 64 * q;
+        if (jq >= N) continue;
+        const uint64_t m = s_occ[jq];
+        const int n = __popcll(m & range);
+        const int o = s_off[jq] + __popcll(m & below(lo));
+        for (int t0 = 0; t0 < n; t0 += 8) {   // loads ahead of the ordered adds, as in (b)
+          float gq[8];
+          uint32_t eq[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              const int p = s_list[o + min(t0 + u, n - 1)];
-              gq[u] = s_g[p];
-              eq[u] = s_ent[p];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              if (t0 + u < n) {
-                if ((int)((eq[u] >> 10) & 31u) < k0) inS0r |= 1u << q;
-                if (!dense) sr[q] = sr[q] + gq[u];
-              }
-            }
+          for (int u = 0; u < 8; ++u) {
+            const int p = s_list[o + min(t0 + u, n - 1)];
+            gq[u] = s_g[p];
+            eq[u] = s_ent[p];
           }
-          if (n > 0) inUr |= 1u << q;
-        }
-      } else {
-        for (int p = lo * k; p < hi * k; ++p) {
-          const uint32_t ent = s_ent[p];
-          if (ent == kNoEntry || (int)(ent & 63u) != lane) continue;
-          const int qe = (int)((ent & 1023u) >> 6);
 #pragma unroll
-          for (int q = 0; q < Q; ++q) {
-            if (q == qe) {
-              inUr |= 1u << q;
-              if ((int)((ent >> 10) & 31u) < k0) inS0r |= 1u << q;
-              if (!dense) sr[q] = sr[q] + s_g[p];
+          for (int u = 0; u < 8; ++u) {
+            if (t0 + u < n) {
+              if ((int)((eq[u] >> 10) & 31u) < k0) inS0r |= 1u << q;
+              if (!dense) sr[q] = sr[q] + gq[u];
             }
           }
         }
+        if (n > 0) inUr |= 1u << q;
       }
       if (dense)
         for (int i = lo; i < hi; ++i)
@@ -823,173 +959,16 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   }
   __syncthreads();
 
-  // ---- (d) batch greedy (Algorithm 1 with a fixed budget; Algorithm 4's final stage):
-  //      order (tier, score desc, index asc), keep the first budget_eff candidates.
-  //      Key: (3 - tier) << 42 | ord(score) << 10 | (1023 - j); candidates are compacted
-  //      and each counts the candidates ahead of it.
-  bool sel = false;
-  int n_s0 = 0, n_start = 0, n_u = 0, m_eff = 0, max_load = 0;
-  if (!ep) {
-    int tier = 3;
-    uint64_t mykey = 0;
-    if (j < N) {
-      const bool cand = dense ? (T > 0) : inU;
-      tier = inS0 ? 0 : (s_tier1[j] ? 1 : (cand ? 2 : 3));
-      if (tier < 3)
-        mykey = ((uint64_t)(3 - tier) << 42) | ((uint64_t)ord(s) << 10) | (uint64_t)(1023 - j);
-      if (tier == 0) atomicAdd(&s_cnt[1], 1);
-      if (tier <= 1) atomicAdd(&s_cnt[2], 1);
-      if (inU) atomicAdd(&s_cnt[3], 1);
-    }
-    int n_cand = 0;
-    const int cpos = block_excl_scan(mykey != 0 ? 1 : 0, s_wsum, n_cand);
-    if (mykey != 0) s_key[cpos] = mykey;
-    if (tid == 0 && (n_cand & 1)) s_key[n_cand] = 0;
-    __syncthreads();
-    n_s0 = s_cnt[1];
-    n_start = s_cnt[2];
-    n_u = s_cnt[3];
-    int rank = 0;
-    if (mykey != 0) {
-      const ulonglong2* keys2 = reinterpret_cast<const ulonglong2*>(s_key);
-      const int n2 = (n_cand + 1) >> 1;
-      for (int jj = 0; jj < n2; ++jj) {
-        const ulonglong2 kk = keys2[jj];
-        rank += (kk.x > mykey) + (kk.y > mykey);
-      }
-    }
-    if (a.budget_mode == 3) {
-      // Algorithm 1's threshold rule: the starting set (ranks below n_start) and then the
-      // candidates in rank order join while f(S) < tau * f(E).  One thread replays the fp32
-      // sums in the stated order: f(E) over every expert in index order, f(S) in rank order.
-      float* const by_index = reinterpret_cast<float*>(s_gcand);
-      float* const by_rank = reinterpret_cast<float*>(s_hist);
-      if (j < N) by_index[j] = s;
-      if (j >= N && j < ((N + 3) & ~3)) by_index[j] = 0.0f;   // pad to whole float4s
-      if (mykey != 0) by_rank[rank] = s;
-      __syncthreads();
-      if (tid == 0) {
-        // sequential fp32 sums; 16-byte LDS reads keep the loads ahead of the adds
-        const float4* e4 = reinterpret_cast<const float4*>(by_index);
-        float f_E = 0.0f;
-#pragma unroll 4
-        for (int q = 0; q < (N + 3) / 4; ++q) {
-          const float4 v = e4[q];
-          f_E = f_E + v.x;
-          f_E = f_E + v.y;
-          f_E = f_E + v.z;
-          f_E = f_E + v.w;
-        }
-        const float target = a.tau * f_E;
-        float f_S = 0.0f;
-        for (int r = 0; r < n_start; ++r) f_S = f_S + by_rank[r];
-        int m = n_start;
-        while (m < n_cand && f_S < target) f_S = f_S + by_rank[m++];
-        s_cnt[6] = m;
-      }
-      __syncthreads();
-      m_eff = max(s_cnt[6], min(k, n_cand));
-    } else {
-      const int base = a.budget_mode == 0 ? a.budget : n_start + a.budget;
-      m_eff = max(min(base, n_cand), min(k, n_cand));
-    }
-    sel = mykey != 0 && rank < m_eff;
-  } else {
-    // GPU groups (Algorithms 5 and 6).  Group g can take a_g = m_g - |S_0 on g| experts
-    // (m_g caps every group's load, Eq. (5)), one per round, best first; its candidate of
-    // rank r (score desc, index asc, among its candidates outside S_0) is taken in round
-    // r + 1 if r < a_g.  The loop stops after the fewest rounds R that bring |S| to m_g * G,
-    // or when no group can take more; so S = S_0 plus every takeable candidate of rank < R,
-    // and R follows from a prefix count of the takeable candidates by rank.
-    const int G = a.G, m_g = a.budget;
-    const int gj = j < N ? (a.group ? a.group[j] : j / (N / G)) : 0;
-    const bool cand = j < N && (dense ? (T > 0) : inU);
-    const bool pick = cand && !inS0;
-    if (j < N) {
-      if (inS0) {
-        atomicAdd(&s_gload[gj], 1);
-        atomicAdd(&s_cnt[1], 1);
-      }
-      if (pick) atomicAdd(&s_gcand[gj], 1);
-      if (inU) atomicAdd(&s_cnt[3], 1);
-      if (cand) atomicAdd(&s_cnt[5], 1);
-    }
-    // key: group << 44 | ord(score) << 10 | (1023 - j); the rank counts the group's keys above
-    const uint64_t pkey =
-        pick ? ((uint64_t)gj << 44) | ((uint64_t)ord(s) << 10) | (uint64_t)(1023 - j) : 0;
-    int n_pick = 0;
-    const int ppos = block_excl_scan(pick ? 1 : 0, s_wsum, n_pick);
-    if (pick) s_key[ppos] = pkey;
-    if (tid == 0 && (n_pick & 1)) s_key[n_pick] = 0;
-    __syncthreads();
-    int rank = 0;
-    bool takeable = false;
-    if (pick) {
-      const ulonglong2* keys2 = reinterpret_cast<const ulonglong2*>(s_key);
-      const uint64_t mine = (uint64_t)gj;
-      const int n2 = (n_pick + 1) >> 1;
-      for (int jj = 0; jj < n2; ++jj) {
-        const ulonglong2 kk = keys2[jj];
-        rank += ((kk.x >> 44) == mine && kk.x > pkey) + ((kk.y >> 44) == mine && kk.y > pkey);
-      }
-      takeable = rank < m_g - s_gload[gj];
-      if (takeable) atomicAdd(&s_hist[rank], 1);
-    }
-    __syncthreads();
-    n_s0 = s_cnt[1];
-    n_u = s_cnt[3];
-    const int n_cand = s_cnt[5];
-    const int need = m_g * G - n_s0;          // picks the rounds must reach
-    static_assert(kThreads == kMaxExperts, "one rank of s_hist per thread");
-    const int at_rank = s_hist[tid];
-    int n_take = 0;
-    const int before = block_excl_scan(at_rank, s_wsum, n_take);
-    if (need > 0 && before < need && before + at_rank >= need) s_cnt[6] = tid + 1;
-    __syncthreads();
-    const int rounds = need <= 0 ? 0 : (n_take < need ? kMaxExperts : s_cnt[6]);
-    sel = inS0 || (takeable && rank < rounds);
-    if (sel) atomicAdd(&s_cnt[2], 1);
-    __syncthreads();
-    // fewer than k experts: the best remaining candidates join regardless of group
-    const int n_loop = s_cnt[2], want = min(k, n_cand);
-    if (n_loop < want) {
-      const bool rest = cand && !sel;
-      const uint64_t fkey = rest ? ((uint64_t)ord(s) << 10) | (uint64_t)(1023 - j) : 0;
-      int n_rest = 0;
-      const int fpos = block_excl_scan(rest ? 1 : 0, s_wsum, n_rest);
-      if (rest) s_key[fpos] = fkey;
-      if (tid == 0 && (n_rest & 1)) s_key[n_rest] = 0;
-      __syncthreads();
-      if (rest) {
-        const ulonglong2* keys2 = reinterpret_cast<const ulonglong2*>(s_key);
-        int r2 = 0;
-        const int n2 = (n_rest + 1) >> 1;
-        for (int jj = 0; jj < n2; ++jj) {
-          const ulonglong2 kk = keys2[jj];
-          r2 += (kk.x > fkey) + (kk.y > fkey);
-        }
-        sel = r2 < want - n_loop;
-      }
-    }
-    // Load_g(S) and MaxLoad(S) (Section 5.1)
-    if (tid < G) s_gload[tid] = 0;
-    __syncthreads();
-    if (sel) atomicAdd(&s_gload[gj], 1);
-    __syncthreads();
-    if (tid < G) {
-      if (a.group_load) a.group_load[tid] = s_gload[tid];
-      atomicMax(&s_cnt[0], s_gload[tid]);
-    }
-    n_start = n_s0;
-    m_eff = min(m_g * G, N);
-  }
+  // ---- (d) batch greedy
+  int max_load = 0, n_s0 = 0, n_start = 0, n_u = 0, m_eff = 0;
+  const bool sel = select_set(a, sh, j < N && s_tier1[j], s, inU, inS0, n_s0, n_start, n_u, m_eff);
   if (j < N) {
     s_sel[j] = sel;
     a.sel_mask[j] = sel;
-    if (sel) atomicAdd(&s_cnt[4], 1);
+    if (sel) atomicAdd(&sh.cnt[4], 1);
   }
   __syncthreads();
-  if (ep) max_load = s_cnt[0];
+  if (ep) max_load = sh.cnt[0];
 
   // ---- (e) refinement: every token to its top-k inside S, gates renormalised (Section 3.4).
   //      The token's plain top-k experts that are in S are its first refined ranks (in
@@ -1105,95 +1084,26 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
     }
   } else if (halves) {
     if constexpr (kHalves) {
-      if (cached_p) {
 #pragma unroll
-        for (int it = 0; it < kCacheP; ++it)
-          if (wave + it * kWaves < n_pairs) refine_pair(wave + it * kWaves, kcp[it]);
-      } else {
-        if (wave < n_pairs) load_pair<Q2>(a, wave, sl, hh, rawp_next);
-        for (int p = wave; p < n_pairs; p += kWaves) {
-          float raw[Q2];
-          uint32_t key[Q2];
-#pragma unroll
-          for (int q = 0; q < Q2; ++q) raw[q] = rawp_next[q];
-          if (p + kWaves < n_pairs) load_pair<Q2>(a, p + kWaves, sl, hh, rawp_next);
-          const int i = 2 * p + hh;
-          const bool valid = i < T;
-#pragma unroll
-          for (int q = 0; q < Q2; ++q)
-            key[q] = (valid && sl + 32 * q < N) ? ord(raw[q] + 0.0f) : 0u;
-          const uint32_t vent = (valid && sl < k) ? (uint32_t)s_ent[i * k + sl] : kNoEntry;
-          const int vid = vent == kNoEntry ? -1 : (int)(vent & 1023u);
-          for (int r = 0; r < k; ++r) {   // the plain top-k is not searched again
-            const int v0 = __builtin_amdgcn_readlane(vid, r);
-            const int v1 = __builtin_amdgcn_readlane(vid, 32 + r);
-            const int vr = hh ? v1 : v0;
-            const bool drop = vr >= 0 && (vr & 31) == sl;
-#pragma unroll
-            for (int q = 0; q < Q2; ++q) key[q] = (drop && q == (vr >> 5)) ? 0u : key[q];
-          }
-          refine_pair(p, key);
-        }
-      }
+      for (int it = 0; it < kCacheP; ++it)
+        if (wave + it * kWaves < n_pairs) refine_pair(wave + it * kWaves, kcp[it]);
     }
-  } else if (cached) {
+  } else {
 #pragma unroll
     for (int it = 0; it < kCache; ++it)
       if (wave + it * kWaves < T) refine(wave + it * kWaves, kc[it]);
-  } else {
-    if (wave < T) load_row<Q>(a, wave, lane, raw_next);
-    for (int i = wave; i < T; i += kWaves) {
-      float raw[Q], v[Q];
-      uint32_t key[Q];
-#pragma unroll
-      for (int q = 0; q < Q; ++q) raw[q] = raw_next[q];
-      if (i + kWaves < T) load_row<Q>(a, i + kWaves, lane, raw_next);
-      row_keys<Q>(raw, N, lane, v, key);
-      const uint32_t vent = lane < k ? (uint32_t)s_ent[i * k + lane] : kNoEntry;
-      const int vid = vent == kNoEntry ? -1 : (int)(vent & 1023u);
-      for (int r = 0; r < k; ++r) {     // the plain top-k is not searched again
-        const int vr = __builtin_amdgcn_readlane(vid, r);
-        if (vr >= 0 && (vr & 63) == lane) {
-#pragma unroll
-          for (int q = 0; q < Q; ++q)
-            if (q == (vr >> 6)) key[q] = 0;
-        }
-      }
-      refine(i, key);
-    }
   }
   __syncthreads();
 
   // ---- (f) permutation: rows grouped by expert (ascending), tokens ascending inside
-  int cnt = 0, total = 0, off = 0;
-  if (occ) {
-    for (int jj = tid; jj < kMaxExperts; jj += kThreads) s_occ[jj] = 0;
-    __syncthreads();
-    cnt = group_by_expert(s_ent, s_occ, s_off, s_list, s_wsum, TK, k, N, total);
-    if (j < N) {
-      off = s_off[j];
-      for (int q = 0; q < cnt; ++q) a.perm[off + q] = s_list[off + q];
-    }
-  } else {
-    if (j < N) {
-      const uint4* ents = reinterpret_cast<const uint4*>(s_ent);
-      for (int vb = 0; vb < TK8 / 8; ++vb) {
-        const uint4 e4 = ents[vb];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) cnt += entry_is(entry_at(e4, u), j);
-      }
-    }
-    off = block_excl_scan(cnt, s_wsum, total);
-    if (j < N && cnt > 0) {
-      const uint4* ents = reinterpret_cast<const uint4*>(s_ent);
-      int pos = off;
-      for (int vb = 0; vb < TK8 / 8; ++vb) {
-        const uint4 e4 = ents[vb];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (entry_is(entry_at(e4, u), j)) a.perm[pos++] = vb * 8 + u;
-      }
-    }
+  int total = 0, off = 0;
+  for (int jj = tid; jj < kMaxExperts; jj += kThreads) s_occ[jj] = 0;
+  __syncthreads();
+  const int cnt =
+      group_by_expert(s_ent, s_occ, s_off, s_list, sh.wsum, TK, k, N, total);
+  if (j < N) {
+    off = s_off[j];
+    for (int q = 0; q < cnt; ++q) a.perm[off + q] = s_list[off + q];
   }
   // with a local GPU group only that group's experts are listed for the expert GEMMs
   const bool listed = j < N && cnt > 0 &&
@@ -1202,9 +1112,10 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   // The active list puts experts with more than kHeavyRows routed rows first (in expert
   // order), then the others: their GEMM blocks run longest, so they start first instead of
   // trailing the launch.  One scan counts both classes (16 bits each).
+  static_assert(kOccTokens <= kSlotRows, "one slot holds all rows of an expert");
   const bool heavy = listed && cnt > kHeavyRows;
   int packed_total = 0;
-  const int packed = block_excl_scan(listed ? (heavy ? 1 : (1 << 16)) : 0, s_wsum, packed_total);
+  const int packed = block_excl_scan(listed ? (heavy ? 1 : (1 << 16)) : 0, sh.wsum, packed_total);
   const int n_heavy = packed_total & 0xFFFF;
   const int n_active = n_heavy + (packed_total >> 16);
   const int arank = heavy ? (packed & 0xFFFF) : n_heavy + (packed >> 16);
@@ -1215,10 +1126,10 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   }
   if (tid == 0) {
     a.counters[kCntActive] = n_active;
-    a.counters[kCntSelected] = s_cnt[4];
+    a.counters[kCntSelected] = sh.cnt[4];
     a.counters[kCntStatus] = 0;
     if (a.stats) {
-      a.stats[0] = s_cnt[4];
+      a.stats[0] = sh.cnt[4];
       a.stats[1] = n_active;
       a.stats[2] = n_u;
       a.stats[3] = n_s0;
@@ -1229,29 +1140,411 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
     }
     if (a.ledger) {   // running totals over the layers of a pass (global budget K)
       a.ledger[0] += 1;
-      a.ledger[1] += s_cnt[4];
+      a.ledger[1] += sh.cnt[4];
       a.ledger[2] += n_active;
       a.ledger[3] += n_u;
-      a.ledger[5] = max(a.ledger[5], s_cnt[4]);
+      a.ledger[5] = max(a.ledger[5], sh.cnt[4]);
     }
   }
+}
+
+// ---- Batches past the one-workgroup kernel's limit: the same steps as four kernels over the
+// whole GPU.  Only the greedy needs every expert's score in one place, and it is cheap, so
+// each block of the third kernel repeats it for the tokens it refines.
+//   route_tokens_kernel  (a)      one wave per token: its plain top-k and gates
+//   route_scores_kernel  (b), (c) one wave per expert: its batch score, tokens ascending; one
+//                                 wave per request: its picks
+//   route_refine_kernel  (d), (e) per block the greedy, then one wave per token
+//   route_lists_kernel   (f)      per block the expert counts, then one wave per expert
+// One workgroup, where a thread per expert walked all T * k entries, took 20 times as long
+// (selection us, one workgroup -> four kernels): N=256 k=8 T=128 144 -> 22, T=512 532 -> 24;
+// N=128 T=256 267 -> 21; N=8 k=2 T=1024 343 -> 22.  What is left is four launches and the
+// latency of each one's dependent loads.  Between the kernels the plain top-k entries lie in
+// `perm` (rank << 10 | expert, -1 = none) and their gates in `w`, both overwritten with the
+// results later; an expert's score and flags in its `active` record.
+constexpr int kTokThreads = 256;
+constexpr int kTokWaves = kTokThreads / 64;
+constexpr uint32_t kFlagU = 1, kFlagS0 = 2;
+
+__device__ __forceinline__ int rank_before(uint64_t m) {   // set bits of m in lanes below
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+}
+
+// s + v(lane 0) + v(lane 1) + ... in lane order; lanes past the data hold +0.0 (s >= 0 stays
+// as it is).  n: lanes that hold data, for an early end.
+__device__ __forceinline__ float add_lanes(float s, float v, int n) {
+  for (int l0 = 0; l0 < n; l0 += 8) {
+#pragma unroll
+    for (int l = 0; l < 8; ++l) s = s + lane_value(v, l0 + l);
+  }
+  return s;
+}
+
+template <int Q>
+__global__ __launch_bounds__(kTokThreads) void route_tokens_kernel(RouteArgs a) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int T = a.T, N = a.N, k = a.k;
+  // the first block also clears the picks and checks the offsets and the group map (as
+  // route_kernel does); the later kernels read the status
+  if (blockIdx.x == 0) {
+    __shared__ int s_bad;
+    if (tid == 0) s_bad = 0;
+    __syncthreads();
+    for (int j = tid; j < N; j += kTokThreads) a.active[j] = make_int4(0, 0, 0, 0);
+    bool bad = false;
+    if (a.req_offsets) {
+      for (int r = tid; r < a.R; r += kTokThreads) {
+        const int lo = a.req_offsets[r], hi = a.req_offsets[r + 1];
+        bad = bad || !(lo < hi) || lo < 0 || hi > T;
+      }
+      if (tid == 0) bad = bad || a.req_offsets[0] != 0 || a.req_offsets[a.R] != T;
+    }
+    if (a.G > 0 && a.group)
+      for (int j = tid; j < N; j += kTokThreads)
+        bad = bad || a.group[j] < 0 || a.group[j] >= a.G;
+    if (bad) atomicOr(&s_bad, 1);
+    __syncthreads();
+    if (tid == 0) a.counters[kCntStatus] = s_bad;
+  }
+  const int i = blockIdx.x * kTokWaves + wave;
+  if (i >= T) return;
+  float raw[Q], v[Q];
+  uint32_t key[Q];
+  load_row<Q>(a, i, lane, raw);
+  row_keys<Q>(raw, N, lane, v, key);
+  float my_h;
+  int my_j;
+  wave_topk<Q>(key, 0, k, lane, my_h, my_j);
+  const float g = ranked_gate(my_h, lane, k);
+  if (lane < k) {
+    a.perm[i * k + lane] = my_j < 0 ? -1 : (lane << 10) | my_j;
+    a.w[i * k + lane] = g;
+  }
+  if (a.score_mode == 1) {
+    const float m = lane_value(my_h, 0);
+    float e[Q];
+    float z = 0.0f;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      e[q] = (lane + 64 * q < N) ? exp_fixed(v[q] - m) : 0.0f;
+      z = add_lanes(z, e[q], min(64, N - 64 * q));
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (lane + 64 * q < N) a.dense[(size_t)i * N + lane + 64 * q] = e[q] / z;
+  }
+}
+
+// One wave: expert j's entries in token order are gathered into the wave's LDS list (ballots
+// give each entry its place), then their gates are loaded 64 at a time and added in order.
+template <int Q>
+__global__ __launch_bounds__(kTokThreads) void route_scores_kernel(RouteArgs a) {
+  __shared__ uint16_t s_list[kTokWaves][kMaxTokens];   // an expert holds a token at most once
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int T = a.T, N = a.N, k = a.k, k0 = a.k0, TK = T * k;
+  const bool dense = a.score_mode == 1;
+  const int unit = blockIdx.x * kTokWaves + wave;
+  if (unit < N) {
+    const int j = unit;
+    uint16_t* const list = s_list[wave];
+    int cnt = 0;
+    const int4* const ents = reinterpret_cast<const int4*>(a.perm);
+    constexpr int kAhead = 4;                          // 256-entry pieces loaded together
+    for (int b0 = 0; b0 < TK; b0 += 256 * kAhead) {
+      int4 e4[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int p = b0 + 256 * u + 4 * lane;
+        e4[u] = p < TK ? ents[p >> 2] : make_int4(-1, -1, -1, -1);
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int p = b0 + 256 * u + 4 * lane;
+        const int en[4] = {e4[u].x, e4[u].y, e4[u].z, e4[u].w};
+        bool hit[4];
+        int before = 0, all = 0, mine = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          hit[c] = p + c < TK && (en[c] & 0x800003FF) == j;
+          const uint64_t m = __ballot(hit[c]);
+          before += rank_before(m);
+          all += __popcll(m);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (hit[c]) list[cnt + before + mine++] = (uint16_t)(p + c);
+        cnt += all;
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    float s = 0.0f;
+    bool s0 = false;
+    for (int q0 = 0; q0 < cnt; q0 += 64) {
+      const int p = list[min(q0 + lane, cnt - 1)];
+      const float g = q0 + lane < cnt ? a.w[p] : 0.0f;
+      s0 = s0 || p % k < k0;
+      if (!dense) s = add_lanes(s, g, min(64, cnt - q0));
+    }
+    if (dense) {
+      for (int i0 = 0; i0 < T; i0 += 64) {
+        const float g = i0 + lane < T ? a.dense[(size_t)(i0 + lane) * N + j] : 0.0f;
+        s = add_lanes(s, g, min(64, T - i0));
+      }
+    }
+    const bool inS0 = __ballot(s0) != 0;
+    if (lane == 0) {
+      a.active[j].x = __float_as_int(s);
+      a.active[j].y = (int)((cnt > 0 ? kFlagU : 0) | (inS0 ? kFlagS0 : 0));
+    }
+    return;
+  }
+  // per request: S_0(r) plus the m_r best remaining experts of r under the request's own score
+  const int r = unit - N;
+  if (!a.req_offsets || a.m_r <= 0 || r >= a.R || a.counters[kCntStatus]) return;
+  const int lo = a.req_offsets[r], hi = a.req_offsets[r + 1];
+  float sr[Q];
+  unsigned inUr = 0, inS0r = 0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) sr[q] = 0.0f;
+  for (int p0 = lo * k; p0 < hi * k; p0 += 64) {
+    const int p = p0 + lane;
+    const int my_ent = p < hi * k ? a.perm[p] : -1;
+    const float my_g = p < hi * k ? a.w[p] : 0.0f;
+    const int n = min(64, hi * k - p0);
+    for (int l = 0; l < n; ++l) {
+      const int ent = __builtin_amdgcn_readlane(my_ent, l);
+      if (ent < 0) continue;
+      const float g = lane_value(my_g, l);
+      const bool here = (ent & 63) == lane;
+      const int qe = (ent & 1023) >> 6;
+      const bool warm = ((ent >> 10) & 31) < k0;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        if (here && q == qe) {
+          inUr |= 1u << q;
+          if (warm) inS0r |= 1u << q;
+          if (!dense) sr[q] = sr[q] + g;
+        }
+      }
+    }
+  }
+  if (dense)
+    for (int i = lo; i < hi; ++i)
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if (lane + 64 * q < N) sr[q] = sr[q] + a.dense[(size_t)i * N + lane + 64 * q];
+  uint32_t key[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const bool cand = (lane + 64 * q < N) && (dense || ((inUr >> q) & 1u)) &&
+                      !((inS0r >> q) & 1u);
+    key[q] = cand ? ord(sr[q]) : 0u;
+  }
+  for (int t = 0; t < a.m_r; ++t) {
+    uint32_t kb;
+    const int jb = wave_pick<Q>(key, lane, kb);
+    if (jb < 0) break;
+    if (lane == 0) a.active[jb].z = 1;     // several requests may store the same 1
+  }
+}
+
+template <int Q>
+__global__ __launch_bounds__(kThreads) void route_refine_kernel(RouteArgs a) {
+  __shared__ GreedyTables sh;
+  __shared__ uint8_t s_sel[kMaxExperts];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int T = a.T, N = a.N, k = a.k, j = tid;
+  const int i = blockIdx.x * kWaves + wave;
+  const bool first = blockIdx.x == 0;
+  if (a.counters[kCntStatus]) {            // invalid offsets or groups: nothing is selected
+    if (i < T && lane < k) {
+      a.ids[i * k + lane] = -1;
+      a.w[i * k + lane] = 0.0f;
+    }
+    if (first) {
+      if (j < N) a.sel_mask[j] = 0;
+      if (a.group_load && tid < a.G) a.group_load[tid] = 0;
+    }
+    return;
+  }
+  float raw[Q];
+  if (i < T) load_row<Q>(a, i, lane, raw);
+  const int4 rec = j < N ? a.active[j] : make_int4(0, 0, 0, 0);
+  if (tid < 8) sh.cnt[tid] = 0;
+  sh.gload[tid] = 0;
+  sh.gcand[tid] = 0;
+  sh.hist[tid] = 0;
+  __syncthreads();
+  int n_s0 = 0, n_start = 0, n_u = 0, m_eff = 0;
+  const bool sel = select_set(a, sh, rec.z != 0, __int_as_float(rec.x), (rec.y & kFlagU) != 0,
+                              (rec.y & kFlagS0) != 0, n_s0, n_start, n_u, m_eff);
+  if (j < N) {
+    s_sel[j] = sel;
+    if (first) a.sel_mask[j] = sel;
+    if (sel) atomicAdd(&sh.cnt[4], 1);
+  }
+  __syncthreads();
+  if (first && tid == 0) {
+    a.counters[kCntSelected] = sh.cnt[4];
+    a.counters[kCntU] = n_u;
+    a.counters[kCntS0] = n_s0;
+    a.counters[kCntStart] = n_start;
+    a.counters[kCntBudget] = m_eff;
+    a.counters[kCntMaxLoad] = a.G > 0 ? sh.cnt[0] : 0;
+  }
+  if (i >= T) return;
+  uint32_t key[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int jq = lane + 64 * q;
+    key[q] = jq < N && s_sel[jq] ? ord(raw[q] + 0.0f) : 0u;
+  }
+  float my_h;
+  int my_j;
+  wave_topk<Q>(key, 0, k, lane, my_h, my_j);
+  const float g = ranked_gate(my_h, lane, k);
+  if (lane < k) {
+    a.ids[i * k + lane] = my_j;
+    a.w[i * k + lane] = g;
+  }
+}
+
+// Every block counts the rows of all experts (LDS atomics) and scans the counts, so each knows
+// where its experts' rows start; a wave then writes one expert's rows in order.
+__global__ __launch_bounds__(kThreads) void route_lists_kernel(RouteArgs a) {
+  __shared__ __align__(16) uint16_t s_ent[kMaxAssignments];
+  __shared__ int s_cnt[kMaxExperts];
+  __shared__ int s_off[kMaxExperts];
+  __shared__ int s_wsum[kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = tid;
+  const int N = a.N, TK = a.T * a.k;
+  const bool first = blockIdx.x == 0;
+  if (a.counters[kCntStatus]) {
+    if (!first) return;
+    for (int e = tid; e <= N; e += kThreads) a.offsets[e] = 0;
+    if (tid == 0) {
+      a.counters[kCntActive] = 0;
+      a.counters[kCntSelected] = 0;
+      if (a.stats) {
+        a.stats[0] = -1;
+        for (int s = 1; s < 8; ++s) a.stats[s] = 0;
+      }
+      if (a.ledger) {
+        a.ledger[0] += 1;
+        a.ledger[4] += 1;
+      }
+    }
+    return;
+  }
+  s_cnt[tid] = 0;
+  __syncthreads();
+  const int TK8 = (TK + 7) & ~7;           // <= kMaxAssignments, a multiple of 8
+  for (int p = tid; p < TK8; p += kThreads) {
+    const int e = p < TK ? a.ids[p] : -1;
+    s_ent[p] = e < 0 ? (uint16_t)kNoEntry : (uint16_t)e;
+    if (e >= 0) atomicAdd(&s_cnt[e], 1);
+  }
+  __syncthreads();
+  const int cnt = s_cnt[j];                // 0 past N
+  int total = 0;
+  const int off = block_excl_scan(cnt, s_wsum, total);
+  s_off[j] = off;
+  __syncthreads();
+  if (first) {
+    // as route_kernel's list, but an expert of more than kSlotRows rows takes several slots
+    // of nearly equal size
+    const bool listed = cnt > 0 && (a.local_group < 0 ||
+                                    (a.group ? a.group[j] : j / (N / a.G)) == a.local_group);
+    const bool heavy = listed && cnt > kHeavyRows;
+    const int parts = (cnt + kSlotRows - 1) / kSlotRows;
+    int packed_total = 0;
+    const int packed =
+        block_excl_scan(listed ? (heavy ? parts : (1 << 16)) : 0, s_wsum, packed_total);
+    const int n_heavy = packed_total & 0xFFFF;
+    const int at = heavy ? (packed & 0xFFFF) : n_heavy + (packed >> 16);
+    if (j < N) a.offsets[j] = off;
+    if (j == N - 1) a.offsets[N] = off + cnt;
+    if (listed) {
+      for (int c = 0; c < parts; ++c) {
+        const int lo = cnt * c / parts, hi = cnt * (c + 1) / parts;
+        a.active[at + c] = make_int4(j, off + lo, hi - lo, 0);
+      }
+    }
+    block_excl_scan(listed ? 1 : 0, s_wsum, total);     // total: the active experts
+    if (tid == 0) {
+      const int n_sel = a.counters[kCntSelected], n_u = a.counters[kCntU];
+      a.counters[kCntActive] = n_heavy + (packed_total >> 16);
+      if (a.stats) {
+        a.stats[0] = n_sel;
+        a.stats[1] = total;
+        a.stats[2] = n_u;
+        a.stats[3] = a.counters[kCntS0];
+        a.stats[4] = a.counters[kCntStart];
+        a.stats[5] = a.counters[kCntBudget];
+        a.stats[6] = a.counters[kCntMaxLoad];
+        a.stats[7] = 0;
+      }
+      if (a.ledger) {
+        a.ledger[0] += 1;
+        a.ledger[1] += n_sel;
+        a.ledger[2] += total;
+        a.ledger[3] += n_u;
+        a.ledger[5] = max(a.ledger[5], n_sel);
+      }
+    }
+  }
+  const int e = blockIdx.x * kWaves + wave;
+  if (e >= N || s_cnt[e] == 0) return;
+  int at = s_off[e];
+  for (int b0 = 0; b0 < TK8; b0 += 512) {
+    const int p = b0 + 8 * lane;
+    uint4 v = make_uint4(~0u, ~0u, ~0u, ~0u);
+    if (p < TK8) v = *reinterpret_cast<const uint4*>(s_ent + p);
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    bool hit[8];
+    int before = 0, all = 0;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      hit[c] = ((w[c >> 1] >> (16 * (c & 1))) & 0xFFFFu) == (uint32_t)e;
+      const uint64_t m = __ballot(hit[c]);
+      before += rank_before(m);
+      all += __popcll(m);
+    }
+    int mine = at + before;
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      if (hit[c]) a.perm[mine++] = p + c;
+    at += all;
+  }
+}
+
+template <int Q>
+hipError_t launch_route_q(const RouteArgs& a, hipStream_t stream) {
+  if (a.T <= small_tokens<Q>()) {
+    hipLaunchKernelGGL(route_kernel<Q>, dim3(1), dim3(kThreads), 0, stream, a);
+    return hipGetLastError();
+  }
+  const int units = a.N + (a.req_offsets && a.m_r > 0 ? a.R : 0);
+  hipLaunchKernelGGL(route_tokens_kernel<Q>, dim3((a.T + kTokWaves - 1) / kTokWaves),
+                     dim3(kTokThreads), 0, stream, a);
+  hipLaunchKernelGGL(route_scores_kernel<Q>, dim3((units + kTokWaves - 1) / kTokWaves),
+                     dim3(kTokThreads), 0, stream, a);
+  hipLaunchKernelGGL(route_refine_kernel<Q>, dim3((a.T + kWaves - 1) / kWaves), dim3(kThreads), 0,
+                     stream, a);
+  hipLaunchKernelGGL(route_lists_kernel, dim3((a.N + kWaves - 1) / kWaves), dim3(kThreads), 0,
+                     stream, a);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_route(const RouteArgs& a, hipStream_t stream) {
-  const dim3 grid(1), block(kThreads);
-  if (a.N <= 64)
-    hipLaunchKernelGGL(route_kernel<1>, grid, block, 0, stream, a);
-  else if (a.N <= 128)
-    hipLaunchKernelGGL(route_kernel<2>, grid, block, 0, stream, a);
-  else if (a.N <= 256)
-    hipLaunchKernelGGL(route_kernel<4>, grid, block, 0, stream, a);
-  else if (a.N <= 512)
-    hipLaunchKernelGGL(route_kernel<8>, grid, block, 0, stream, a);
-  else
-    hipLaunchKernelGGL(route_kernel<16>, grid, block, 0, stream, a);
-  return hipGetLastError();
+  if (a.N <= 64) return launch_route_q<1>(a, stream);
+  if (a.N <= 128) return launch_route_q<2>(a, stream);
+  if (a.N <= 256) return launch_route_q<4>(a, stream);
+  if (a.N <= 512) return launch_route_q<8>(a, stream);
+  return launch_route_q<16>(a, stream);
 }
 
 }  // namespace xs
