@@ -350,7 +350,8 @@ xshare_status layer_common(const xshare_layer_args& a) {
   fa.est_active = params->budget_mode == XSHARE_BUDGET_THRESHOLD
                       ? 0
                       : layer_estimate(T, params, a.ep);
-  fa.shared_slots = n_shared * ((T + xs::kSlotRows - 1) / xs::kSlotRows);
+  fa.shared_parts = (T + xs::kSlotRows - 1) / xs::kSlotRows;
+  fa.shared_slots = n_shared * fa.shared_parts;
   fa.splits = wt.fmt == XSHARE_WEIGHTS_MXFP4 ? L.q4_splits : L.splits;
   fa.gu_splits = L.gu_splits;
   fa.gu_tail_splits = L.gu_tail_splits;

@@ -19,8 +19,10 @@
 // dimension (16 per tile, up to two tiles per pass), accumulation is fp32.  The block's
 // four waves share the expert and its token rows, which the block stages in LDS one step
 // at a time (block_pass); the next step's loads are issued before the current step's
-// MFMAs (register double buffering).  The per-wave passes (wave_pass*) serve the router
-// GEMM and the shapes the staged pass does not take.
+// MFMAs (register double buffering).  A reduction that is no multiple of the step ends in a
+// partial step of whole 32-element MFMAs (kRest), for any d and f the library takes: with a
+// step that divides them instead (32 elements and per-wave token loads for odd multiples of
+// 32) T=37 N=60 k=6 d=2720 f=1376 M=30 took 190 us a layer, now 162.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -192,143 +194,54 @@ __device__ __forceinline__ void store_hilo(uint16_t* h2, size_t p, int c, int f,
   at[8] = to_bf16(v - from_bf16(h));
 }
 
-// One pass of a wave over the reduction dimension K for up to kTiles token tiles:
-// acc[m][rt] += A_rt (16 x K) * B_m^T (K x 16) for the NM weight matrices B_m.
-// `arow[rt]` points at the token row this lane feeds (a duplicate of a valid row for
-// padding lanes, whose output rows are discarded; duplicate addresses coalesce, which
-// measured faster than masking those lanes), `brow[m]` at the weight row of this lane's
-// column;
-// both already offset by this lane's group position g * 8U.  Weight loads (HBM) run one
-// step ahead; token loads (L2-resident) are issued either one step ahead too (ADBL) or
-// at the top of their own step, which halves their register footprint.
-// AS: element stride of the token rows per k (2 for the interleaved hi / lo rows, whose
-// 8-element chunks alternate).
-#ifndef XS_KMAP
-#define XS_KMAP 1
-#endif
-// Reduction offsets of the bf16 passes: MFMA u of a step and lane group g.  With XS_KMAP 1
-// the four lane groups of one MFMA read 32 contiguous elements, so one load instruction
-// touches half as many cache lines as with 0 (each lane's U MFMAs on 8U contiguous
-// elements); measured 0.3-1.2 % faster.  A and B use the same map, so the sum is the same.
-__device__ __forceinline__ constexpr int kstep(int u) { return XS_KMAP ? 32 * u : 8 * u; }
+// Reduction offsets of the bf16 passes: MFMA u of a step and lane group g.  The four lane
+// groups of one MFMA read 32 contiguous elements, so one load instruction touches half as many
+// cache lines as with 8U contiguous elements a lane; measured 0.3-1.2 % faster.
+__device__ __forceinline__ constexpr int kstep(int u) { return 32 * u; }
+__device__ __forceinline__ constexpr int klane(int g) { return 8 * g; }
+
+// One pass of a wave of the router GEMM over the reduction dimension K for up to kTiles token
+// tiles: acc[rt] += A_rt (16 x K) * B^T (K x 16).  `arow[rt]` points at the token row this lane
+// feeds (a duplicate of a valid row for padding lanes, whose output rows are discarded;
+// duplicate addresses coalesce, which measured faster than masking those lanes), `brow` at the
+// weight row of this lane's column; both already offset by klane.  Loads run one step ahead.
 template <int U>
-__device__ __forceinline__ constexpr int klane(int g) { return XS_KMAP ? 8 * g : 8 * U * g; }
-
-template <int U, int NM, bool ADBL, int TL = kTiles, int AS = 1>
-__device__ __forceinline__ void wave_pass(const uint16_t* const (&arow)[TL], int nt,
-                                          const uint16_t* const (&brow)[NM], int K,
-                                          floatx4 (&acc)[NM][TL], int k_first = 0) {
+__device__ __forceinline__ void wave_pass(const uint16_t* const (&arow)[kTiles], int nt,
+                                          const uint16_t* brow, int K, floatx4 (&acc)[kTiles]) {
   constexpr int KB = 32 * U;
-  bf16x8 b[NM][U], x[TL][U];
+  bf16x8 b[U], x[kTiles][U];
 #pragma unroll
-  for (int m = 0; m < NM; ++m)
+  for (int u = 0; u < U; ++u) b[u] = load8(brow + kstep(u));
 #pragma unroll
-    for (int u = 0; u < U; ++u) b[m][u] = load8(brow[m] + k_first + kstep(u));
-  if (ADBL) {
+  for (int rt = 0; rt < kTiles; ++rt)
+    if (rt < nt)
 #pragma unroll
-    for (int rt = 0; rt < TL; ++rt)
-      if (rt < nt)
-#pragma unroll
-        for (int u = 0; u < U; ++u) x[rt][u] = load8(arow[rt] + AS * (k_first + kstep(u)));
-  }
-
-  int kb = k_first;
-  for (int s = 0; s < K; s += KB) {
-    bf16x8 nb[NM][U], nx[ADBL ? TL : 1][U];
-    const bool more = s + KB < K;
-    int kn = kb + KB;
-    if (kn >= K) kn -= K;
-    // Token loads of this step go out before the next step's weight loads: loads complete
-    // in issue order, so waiting for the tokens then leaves the weight prefetch in flight.
-    if (!ADBL) {
-#pragma unroll
-      for (int rt = 0; rt < TL; ++rt)
-        if (rt < nt)
-#pragma unroll
-          for (int u = 0; u < U; ++u) x[rt][u] = load8(arow[rt] + AS * (kb + kstep(u)));
-    }
+      for (int u = 0; u < U; ++u) x[rt][u] = load8(arow[rt] + kstep(u));
+  for (int kb = 0; kb < K; kb += KB) {
+    bf16x8 nb[U], nx[kTiles][U];
+    const bool more = kb + KB < K;
     if (more) {
 #pragma unroll
-      for (int m = 0; m < NM; ++m)
+      for (int u = 0; u < U; ++u) nb[u] = load8(brow + kb + KB + kstep(u));
 #pragma unroll
-        for (int u = 0; u < U; ++u) nb[m][u] = load8(brow[m] + kn + kstep(u));
-      if (ADBL) {
+      for (int rt = 0; rt < kTiles; ++rt)
+        if (rt < nt)
 #pragma unroll
-        for (int rt = 0; rt < TL; ++rt)
-          if (rt < nt)
-#pragma unroll
-            for (int u = 0; u < U; ++u) nx[rt][u] = load8(arow[rt] + AS * (kn + kstep(u)));
-      }
+          for (int u = 0; u < U; ++u) nx[rt][u] = load8(arow[rt] + kb + KB + kstep(u));
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int rt = 0; rt < TL; ++rt)
-        if (rt < nt)
-#pragma unroll
-          for (int m = 0; m < NM; ++m) acc[m][rt] = mfma(x[rt][u], b[m][u], acc[m][rt]);
+      for (int rt = 0; rt < kTiles; ++rt)
+        if (rt < nt) acc[rt] = mfma(x[rt][u], b[u], acc[rt]);
     if (more) {
 #pragma unroll
-      for (int m = 0; m < NM; ++m)
+      for (int u = 0; u < U; ++u) b[u] = nb[u];
 #pragma unroll
-        for (int u = 0; u < U; ++u) b[m][u] = nb[m][u];
-      if (ADBL) {
+      for (int rt = 0; rt < kTiles; ++rt)
 #pragma unroll
-        for (int rt = 0; rt < TL; ++rt)
-#pragma unroll
-          for (int u = 0; u < U; ++u) x[rt][u] = nx[ADBL ? rt : 0][u];
-      }
+        for (int u = 0; u < U; ++u) x[rt][u] = nx[rt][u];
     }
-    kb = kn;
-  }
-}
-
-// wave_pass with FP8 weights: the B operand comes from E4M3 codes (8 bytes per lane and
-// MFMA), prefetched one step ahead as raw bytes and converted to bf16 just before use.
-template <int U, int NM, int TL = kTiles, int AS = 1>
-__device__ __forceinline__ void wave_pass_q8(const uint16_t* const (&arow)[TL], int nt,
-                                             const uint8_t* const (&brow)[NM], int K,
-                                             floatx4 (&acc)[NM][TL], int k_first = 0) {
-  constexpr int KB = 32 * U;
-  uint2 b[NM][U];
-  bf16x8 x[TL][U];
-#pragma unroll
-  for (int m = 0; m < NM; ++m)
-#pragma unroll
-    for (int u = 0; u < U; ++u) b[m][u] = load_q8(brow[m] + k_first + 8 * u);
-  int kb = k_first;
-  for (int s = 0; s < K; s += KB) {
-    uint2 nb[NM][U];
-    const bool more = s + KB < K;
-    int kn = kb + KB;
-    if (kn >= K) kn -= K;
-#pragma unroll
-    for (int rt = 0; rt < TL; ++rt)       // tokens first: see wave_pass
-      if (rt < nt)
-#pragma unroll
-        for (int u = 0; u < U; ++u) x[rt][u] = load8(arow[rt] + AS * (kb + 8 * u));
-    if (more) {
-#pragma unroll
-      for (int m = 0; m < NM; ++m)
-#pragma unroll
-        for (int u = 0; u < U; ++u) nb[m][u] = load_q8(brow[m] + kn + 8 * u);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int m = 0; m < NM; ++m) {
-        const bf16x8 bv = fp8x8_to_bf16(b[m][u]);
-#pragma unroll
-        for (int rt = 0; rt < TL; ++rt)
-          if (rt < nt) acc[m][rt] = mfma(x[rt][u], bv, acc[m][rt]);
-      }
-    if (more) {
-#pragma unroll
-      for (int m = 0; m < NM; ++m)
-#pragma unroll
-        for (int u = 0; u < U; ++u) b[m][u] = nb[m][u];
-    }
-    kb = kn;
   }
 }
 
@@ -354,67 +267,6 @@ __device__ __forceinline__ uint32_t load_mx_scales(const uint8_t* row, int k) {
     return *reinterpret_cast<const uint16_t*>(p);
   else
     return *p;
-}
-
-// wave_pass with MXFP4 weights: per step a lane loads 4U bytes of codes (its 8U elements)
-// and their scale bytes, one step ahead; the codes become bf16, scaled, just before use.
-// `brow[m]` points at the codes of this lane's first element, `srow[m]` at its row's tiled
-// scales (mx_row); `kl`: this lane's first input (absolute, for the scale bytes).
-template <int U, int NM, int TL = kTiles, int AS = 1>
-__device__ __forceinline__ void wave_pass_q4(const uint16_t* const (&arow)[TL], int nt,
-                                             const uint8_t* const (&brow)[NM],
-                                             const uint8_t* const (&srow)[NM], int kl, int K,
-                                             floatx4 (&acc)[NM][TL], int k_first = 0) {
-  static_assert(U == 1 || U == 2 || U == 4 || U == 8, "1, 2, 4 or 8 words per lane and step");
-  constexpr int KB = 32 * U;
-  Q4<U> b[NM];
-  uint32_t e[NM];
-  bf16x8 x[TL][U];
-#pragma unroll
-  for (int m = 0; m < NM; ++m) {
-    b[m] = load_q4<U>(brow[m] + k_first / 2);
-    e[m] = load_mx_scales<U>(srow[m], kl + k_first);
-  }
-  int kb = k_first;
-  for (int s = 0; s < K; s += KB) {
-    Q4<U> nb[NM];
-    uint32_t ne[NM];
-    const bool more = s + KB < K;
-    int kn = kb + KB;
-    if (kn >= K) kn -= K;
-#pragma unroll
-    for (int rt = 0; rt < TL; ++rt)       // tokens first: see wave_pass
-      if (rt < nt)
-#pragma unroll
-        for (int u = 0; u < U; ++u) x[rt][u] = load8(arow[rt] + AS * (kb + 8 * u));
-    if (more) {
-#pragma unroll
-      for (int m = 0; m < NM; ++m) {
-        nb[m] = load_q4<U>(brow[m] + kn / 2);
-        ne[m] = load_mx_scales<U>(srow[m], kl + kn);
-      }
-    }
-#pragma unroll
-    for (int m = 0; m < NM; ++m) {
-      const float sc0 = e8m0_scale(e[m] & 0xFFu);
-      const float sc1 = U == 8 ? e8m0_scale((e[m] >> 8) & 0xFFu) : sc0;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bf16x8 bv = fp4x8_to_bf16(b[m].w[u], u < 4 ? sc0 : sc1);
-#pragma unroll
-        for (int rt = 0; rt < TL; ++rt)
-          if (rt < nt) acc[m][rt] = mfma(x[rt][u], bv, acc[m][rt]);
-      }
-    }
-    if (more) {
-#pragma unroll
-      for (int m = 0; m < NM; ++m) {
-        b[m] = nb[m];
-        e[m] = ne[m];
-      }
-    }
-    kb = kn;
-  }
 }
 
 // Token rows staged in LDS.  With tokens loaded per wave (wave_pass*), every wave of a block
@@ -449,14 +301,17 @@ struct Stage {
 // lane's first element; sc: MXFP4 scale bytes), the registers that hold them, their loads
 // for step s and the B operand of MFMA u.  `koff(g, u)`: the reduction offset, within a
 // step, of lane group g's elements in MFMA u (the A operand reads the same).
+// The `rest` members serve the last, partial step of a reduction that is no multiple of the
+// step: `ut` MFMAs of 32 elements (1 <= ut < U), elements 32u + 8g of each lane group, so that
+// every lane of an MFMA has elements and nothing past the row is read.
 template <int kW, int U>
 struct WTile;
 template <int U>
 struct WTile<kBf16, U> {
-  using GV = uint32_t;
   struct Ptr { const uint16_t* w; };
   struct Regs { bf16x8 w[U]; };
-  __device__ static constexpr int koff(int g, int u) { return kstep(u) + klane<U>(g); }
+  using Rest = Regs;
+  __device__ static constexpr int koff(int g, int u) { return kstep(u) + klane(g); }
   __device__ static Regs load(const Ptr& p, int s) {
     Regs r;
 #pragma unroll
@@ -464,12 +319,19 @@ struct WTile<kBf16, U> {
     return r;
   }
   __device__ static bf16x8 operand(const Regs& r, int u) { return r.w[u]; }
+  __device__ static Rest load_rest(const Ptr& p, int s, int, int ut) {
+    Rest r;
+#pragma unroll
+    for (int u = 0; u < U; ++u) r.w[u] = load8(p.w + s + 32 * min(u, ut - 1));
+    return r;
+  }
+  __device__ static bf16x8 operand_rest(const Rest& r, int u) { return r.w[u]; }
 };
 template <int U>
 struct WTile<kFp8, U> {
-  using GV = uint32_t;
   struct Ptr { const uint8_t* w; };
   struct Regs { uint2 w[U]; };
+  using Rest = Regs;
   __device__ static constexpr int koff(int g, int u) { return 8 * U * g + 8 * u; }
   __device__ static Regs load(const Ptr& p, int s) {
     Regs r;
@@ -478,6 +340,14 @@ struct WTile<kFp8, U> {
     return r;
   }
   __device__ static bf16x8 operand(const Regs& r, int u) { return fp8x8_to_bf16(r.w[u]); }
+  __device__ static Rest load_rest(const Ptr& p, int s, int g, int ut) {
+    const uint8_t* const w = p.w - (8 * U - 8) * g + s;
+    Rest r;
+#pragma unroll
+    for (int u = 0; u < U; ++u) r.w[u] = load_q8(w + 32 * min(u, ut - 1));
+    return r;
+  }
+  __device__ static bf16x8 operand_rest(const Rest& r, int u) { return operand(r, u); }
 };
 template <int U>
 struct WTile<kMx4, U> {
@@ -485,8 +355,10 @@ struct WTile<kMx4, U> {
   struct Ptr { const uint8_t* w; const uint8_t* sc; int k; };
   // scale bytes (block u / 4 in byte u / 4) in a type no wider than their load: a widening
   // at the end of a step would wait for the load
-  using E = typename std::conditional<(U > 8), uint32_t, uint16_t>::type;
+  using E = typename std::conditional<(U > 8), uint32_t,
+                                      typename std::conditional<(U == 8), uint16_t, uint8_t>::type>::type;
   struct Regs { Q4<U> q; E e; };
+  struct Rest { uint32_t w[U]; uint8_t e[U]; };
   __device__ static constexpr int koff(int g, int u) { return 8 * U * g + 8 * u; }
   __device__ static Regs load(const Ptr& p, int s) {
     Regs r;
@@ -498,13 +370,27 @@ struct WTile<kMx4, U> {
     const uint32_t e = r.e;
     return fp4x8_to_bf16(r.q.w[u], e8m0_scale((e >> (8 * (u >> 2))) & 0xFFu));
   }
+  __device__ static Rest load_rest(const Ptr& p, int s, int g, int ut) {
+    const uint8_t* const w = p.w - (4 * U - 4) * g + s / 2;
+    const int k = p.k - 8 * U * g + s;
+    Rest r;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      r.w[u] = *reinterpret_cast<const uint32_t*>(w + 16 * min(u, ut - 1));
+      r.e[u] = (uint8_t)load_mx_scales<1>(p.sc, k + 32 * min(u, ut - 1));
+    }
+    return r;
+  }
+  __device__ static bf16x8 operand_rest(const Rest& r, int u) {
+    return fp4x8_to_bf16(r.w[u], e8m0_scale(r.e[u]));
+  }
 };
 
 // NT: token tiles of the pass (R <= TR * NT rows); NL: loads per thread and step, at least
 // ceil(R * P / 256) (pieces beyond R * P repeat the last one).  Staged row r (r < R) is
-// x[tok[r] * ld ...], x already offset to this block's reduction range.  acc[m][rt] as in
-// wave_pass (gate/up) or the down pass.
-template <int kW, int U, bool kDown, int NM, int NT, int NL, int TA>
+// x[tok[r] * ld ...], x already offset to this block's reduction range.  acc[m][rt]: the sums of
+// weight tile m and token tile rt.  kRest: K may be no multiple of the step (k_first is 0).
+template <int kW, int U, bool kDown, int NM, int NT, int NL, bool kRest, int TA>
 __device__ __forceinline__ void block_pass(const uint16_t* x, size_t ld, const int* tok, int R,
                                            const typename WTile<kW, U>::Ptr (&wp)[NM], int K,
                                            int k_first, floatx4 (&acc)[NM][TA], uint16_t* lds) {
@@ -532,6 +418,45 @@ __device__ __forceinline__ void block_pass(const uint16_t* x, size_t ld, const i
 
   u32x4 v[NL];
   typename WT::Regs b[NM];
+  // the partial step's loads (from k = Kf on; a piece past the row reads the row's start, and
+  // no MFMA takes it) and its MFMAs
+  const int Kf = kRest ? K / KB * KB : K, ut = (K - Kf) >> 5;
+  typename WT::Rest rb[kRest ? NM : 1];
+  auto load_rest = [&]() {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int q = min(t + i * kBlock, R * S::P - 1);
+      v[i] = *reinterpret_cast<const u32x4*>(
+          src[i] + (q % S::P < 4 * S::AS * ut ? S::AS * Kf : -(q % S::P) * 8));
+    }
+#pragma unroll
+    for (int m = 0; m < NM; ++m) rb[kRest ? m : 0] = WT::load_rest(wp[m], Kf, g, ut);
+  };
+  auto step_rest = [&](const uint16_t* cur) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (u >= ut) break;
+      const int ka = S::AS * (32 * u + 8 * g);
+      bf16x8 xa[NT];
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) xa[rt] = *reinterpret_cast<const bf16x8*>(cur + rofs[rt] + ka);
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        const bf16x8 bv = WT::operand_rest(rb[kRest ? m : 0], u);
+#pragma unroll
+        for (int rt = 0; rt < NT; ++rt) acc[m][rt] = mfma(xa[rt], bv, acc[m][rt]);
+      }
+    }
+  };
+  if (kRest && Kf == 0) {                  // a reduction shorter than one step
+    load_rest();
+#pragma unroll
+    for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(lds + wofs[i]) = v[i];
+    __syncthreads();
+    step_rest(lds);
+    __syncthreads();
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < NL; ++i) v[i] = *reinterpret_cast<const u32x4*>(src[i] + S::AS * k_first);
 #pragma unroll
@@ -575,15 +500,30 @@ __device__ __forceinline__ void block_pass(const uint16_t* x, size_t ld, const i
   };
   // the pass starts at step k_first and wraps around (two plain loops: a wrap test inside
   // one loop measured slower)
-  for (int kn = k_first + KB; kn < K; kn += KB) advance(kn);
+  for (int kn = k_first + KB; kn < Kf; kn += KB) advance(kn);
   for (int kn = 0; kn < k_first; kn += KB) advance(kn);
-  step(lds + buf * kStageRows * S::LS);
+  if constexpr (kRest) {
+    // not overlapped with the last full step: holding both steps' weights spilled registers
+    // or cost a wave per SIMD
+    step(lds + buf * kStageRows * S::LS);
+    if (ut) {
+      __builtin_amdgcn_sched_barrier(0);
+      load_rest();
+      uint16_t* const nxt = lds + (buf ^ 1) * kStageRows * S::LS;
+#pragma unroll
+      for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(nxt + wofs[i]) = v[i];
+      __syncthreads();
+      step_rest(nxt);
+    }
+  } else {
+    step(lds + buf * kStageRows * S::LS);
+  }
   __syncthreads();                         // the block's next pass rewrites both buffers
 }
 
 // The staged pass over R token rows, by block-uniform instance: the fewest tiles that hold
 // R rows and the loads per thread that the largest R of that tile count needs.
-template <int kW, int U, bool kDown, int NM, int TA>
+template <int kW, int U, bool kDown, int NM, bool kRest, int TA>
 __device__ __forceinline__ void staged_pass(const uint16_t* x, size_t ld, const int* tok,
                                                int R, const typename WTile<kW, U>::Ptr (&wp)[NM],
                                                int K, int k_first, floatx4 (&acc)[NM][TA],
@@ -595,26 +535,26 @@ __device__ __forceinline__ void staged_pass(const uint16_t* x, size_t ld, const 
     constexpr int L1h = (TR / 2 * S::P + kBlock - 1) / kBlock;
     constexpr int L2h = (3 * TR / 2 * S::P + kBlock - 1) / kBlock;
     if (R <= TR / 2)
-      block_pass<kW, U, kDown, NM, 1, L1h, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
+      block_pass<kW, U, kDown, NM, 1, L1h, kRest, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
     else if (R <= TR)
-      block_pass<kW, U, kDown, NM, 1, L1, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
+      block_pass<kW, U, kDown, NM, 1, L1, kRest, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
     else if (R <= 3 * TR / 2)
-      block_pass<kW, U, kDown, NM, 2, L2h, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
+      block_pass<kW, U, kDown, NM, 2, L2h, kRest, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
     else
-      block_pass<kW, U, kDown, NM, 2, L2, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
+      block_pass<kW, U, kDown, NM, 2, L2, kRest, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
   } else {                          // down: up to four 8-token tiles
     static_assert(TA == 2 || TA == 4, "two or four 8-token tiles");
     if (R <= TR) {
-      block_pass<kW, U, kDown, NM, 1, L1, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
+      block_pass<kW, U, kDown, NM, 1, L1, kRest, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
     } else if (TA == 2 || R <= 2 * TR) {
-      block_pass<kW, U, kDown, NM, 2, L2, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
+      block_pass<kW, U, kDown, NM, 2, L2, kRest, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
     } else if constexpr (TA == 4) {
       constexpr int L3 = (3 * TR * S::P + kBlock - 1) / kBlock;
       constexpr int L4 = (4 * TR * S::P + kBlock - 1) / kBlock;
       if (R <= 3 * TR)
-        block_pass<kW, U, kDown, NM, 3, L3, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
+        block_pass<kW, U, kDown, NM, 3, L3, kRest, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
       else
-        block_pass<kW, U, kDown, NM, 4, L4, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
+        block_pass<kW, U, kDown, NM, 4, L4, kRest, TA>(x, ld, tok, R, wp, K, k_first, acc, lds);
     }
   }
 }
@@ -623,14 +563,8 @@ __device__ __forceinline__ void staged_pass(const uint16_t* x, size_t ld, const 
 #ifndef XS_GATE_UP_U
 #define XS_GATE_UP_U 4
 #endif
-#ifndef XS_GATE_UP_ADBL
-#define XS_GATE_UP_ADBL 1
-#endif
 #ifndef XS_DOWN_U
 #define XS_DOWN_U 2
-#endif
-#ifndef XS_DOWN_ADBL
-#define XS_DOWN_ADBL 0
 #endif
 #ifndef XS_Q8_GATE_UP_U
 #define XS_Q8_GATE_UP_U 4
@@ -741,40 +675,36 @@ static_assert(XS_DOWN_XCD_SLOTS >= 8, "at least one slot per XCD");
 #define XS_DOWN_WAVES_PER_EU 2       // waves per SIMD of the staged down instances (3: spills)
 #endif
 
-// Formats whose GEMMs stage the token rows in LDS (bit kW of each mask; all three by
-// default).  Same-box A/B against per-wave token loads, gate/up and down (us):
+// Every format stages the token rows in LDS.  Same-box A/B against per-wave token loads,
+// gate/up and down (us):
 //   bf16  DeepSeek T=32 M=48  469 / 262 -> 460 / 258   M=24  250 / 165 -> 245 / 138
 //         Qwen M=32            64 /  40 ->  53 /  32   DeepSeek T=8  236 / 132 -> 237 / 132
 //   FP8   DeepSeek T=32 M=48  249 / 147 -> 249 / 138   speculative  371 / 209 -> 329 / 189
 //   MXFP4 DeepSeek T=32 M=48  193 / 142 -> 170 /  99   Qwen M=32     44 /  32 ->  25 /  19
-// A staged down pass rotates its start by block, not by wave (the waves of a block share
-// one token step).
-#ifndef XS_STAGE_GATE_UP
-#define XS_STAGE_GATE_UP 7
-#endif
-#ifndef XS_STAGE_DOWN
-#define XS_STAGE_DOWN 7
-#endif
-constexpr bool stage_gate_up(int kW, int U) { return ((XS_STAGE_GATE_UP >> kW) & 1) && U >= 2; }
-constexpr bool stage_down(int kW) { return (XS_STAGE_DOWN >> kW) & 1; }
+// A down pass rotates its start by block, not by wave (the waves of a block share one token
+// step).
 
 // Work of grid row `slot` of the expert GEMMs: the always-on shared experts first (all T
 // tokens, rows T*k + s*T + t, kSlotRows of them a slot at most; their blocks are the longest,
 // so they start first and do not trail the launch), then the routed active experts (their
 // tokens' rows in permuted order).  False for rows beyond both.  `e` is the shared or the
-// routed expert, t0 the first token of a shared slot.
+// routed expert.
 struct SlotWork {
-  int e, p0, te, t0;
+  int e, p0, te;
   bool shared;
 };
 
 __device__ __forceinline__ bool slot_work(const FfnArgs& a, int slot, SlotWork& w) {
   if (slot < a.shared_slots) {
-    const int parts = a.shared_slots / a.n_shared, c = slot % parts;
-    w.e = slot / parts;
-    w.t0 = a.T * c / parts;
-    w.p0 = a.T * a.k + w.e * a.T + w.t0;
-    w.te = a.T * (c + 1) / parts - w.t0;
+    int t0 = 0, t1 = a.T;
+    w.e = slot;
+    if (a.shared_parts > 1) {
+      w.e = slot / a.shared_parts;
+      t0 = a.T * (slot - w.e * a.shared_parts) / a.shared_parts;
+      t1 = a.T * (slot - w.e * a.shared_parts + 1) / a.shared_parts;
+    }
+    w.p0 = a.T * a.k + w.e * a.T + t0;
+    w.te = t1 - t0;
     w.shared = true;
     return true;
   }
@@ -786,7 +716,6 @@ __device__ __forceinline__ bool slot_work(const FfnArgs& a, int slot, SlotWork& 
   w.e = rec.x;
   w.p0 = rec.y;
   w.te = rec.z;
-  w.t0 = 0;
   w.shared = false;
   return true;
 }
@@ -809,10 +738,16 @@ __device__ __forceinline__ const uint8_t* slot_q(const FfnArgs& a, const SlotWor
 // blocks (the launch takes two only for grids that stay large).
 // The MXFP4 one-tile instance is held to 168 registers (3 waves per SIMD): left alone the
 // compiler took 175 and 2 waves, and DeepSeek T=8 gate/up ran 14 % slower.  So are the FP8
-// instances of up to 4 words a step (XS_Q8_GU_W3).
-template <int U, bool kSplit, int kW, int CT>
-__global__ __attribute__((amdgpu_waves_per_eu((kW == kMx4 && CT == 1) ||
-                                               (kW == kFp8 && U <= 4 && XS_Q8_GU_W3) ? 3 : 1)))
+// instances of up to 4 words a step (XS_Q8_GU_W3), but not the two-tile one with a partial
+// step, which would spill.  The other instances with a partial step are held to 2.
+template <int kW, int U, int CT, bool kRest>
+constexpr int gu_waves() {
+  if (kW == kMx4 && CT == 1) return 3;
+  if (kW == kFp8 && U <= 4 && XS_Q8_GU_W3 && !(kRest && CT == 2)) return 3;
+  return kRest && !(kW == kBf16 && CT == 2) ? 2 : 1;
+}
+template <int U, bool kSplit, int kW, int CT, bool kRest>
+__global__ __attribute__((amdgpu_waves_per_eu(gu_waves<kW, U, CT, kRest>())))
 __launch_bounds__(kBlock) void gate_up_kernel(FfnArgs a) {
   constexpr int NM = 2 * CT;                   // weight tiles: W1 and W3 of each column tile
   SlotWork sw;
@@ -821,15 +756,13 @@ __launch_bounds__(kBlock) void gate_up_kernel(FfnArgs a) {
   const int p0 = sw.p0, te = sw.te;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int j0 = (blockIdx.x * kWaves + wave) * kCols * CT;
-  // a staged pass needs the whole block: a wave past f stays for the staging and the
+  // the staged pass needs the whole block: a wave past f stays for the staging and the
   // barriers (its columns are clamped into range and its stores skipped)
-  constexpr bool kStaged = stage_gate_up(kW, U);
-  if (!kStaged && j0 >= a.f) return;
   const int n = lane & 15, g = lane >> 4;
   const int d = a.d, f = a.f;
   const int Kg = kSplit ? d / a.gu_splits : d;   // this block's part of the reduction
   const size_t kbase = kSplit ? (size_t)blockIdx.z * Kg : 0;
-  const size_t k0 = kbase + (size_t)(kW == kBf16 ? klane<U>(g) : g * 8 * U);
+  const size_t k0 = kbase + (size_t)(kW == kBf16 ? klane(g) : g * 8 * U);
   const size_t plane = (size_t)a.part_rows * f;   // one fp32 partial plane [part_rows, f]
   int col[CT];                                 // this lane's column of each tile (< f)
   float sc[NM];                                // FP8 per-row scales (else 1)
@@ -842,80 +775,38 @@ __launch_bounds__(kBlock) void gate_up_kernel(FfnArgs a) {
 
   for (int c0 = 0; c0 < te; c0 += 16 * kTiles) {
     const int nt = min(kTiles, (te - c0 + 15) / 16);
-    const uint16_t* arow[kTiles];
-#pragma unroll
-    for (int rt = 0; rt < kTiles; ++rt) {
-      const int t = min(c0 + rt * 16 + n, te - 1);
-      const int tok = sw.shared ? sw.t0 + t : a.perm[p0 + t] / a.k;
-      arow[rt] = a.x + (size_t)tok * d + k0;
-    }
     floatx4 acc[NM][kTiles];
 #pragma unroll
     for (int m = 0; m < NM; ++m)
 #pragma unroll
       for (int rt = 0; rt < kTiles; ++rt) acc[m][rt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (kStaged) {
-      typename WTile<kW, U>::Ptr wp[NM];
+    typename WTile<kW, U>::Ptr wp[NM];
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const size_t wrow = (size_t)col[ct] * d + k0;
-        if constexpr (kW == kBf16) {
-          wp[2 * ct].w = slot_w(a, sw, a.w1, a.sw1) + wrow;
-          wp[2 * ct + 1].w = slot_w(a, sw, a.w3, a.sw3) + wrow;
-        } else if constexpr (kW == kFp8) {
-          wp[2 * ct].w = slot_q(a, sw, a.q1) + wrow;
-          wp[2 * ct + 1].w = slot_q(a, sw, a.q3) + wrow;
-        } else {        // row col of the expert: d / 2 code bytes; its tiled scale row
-          const size_t r = (size_t)sw.e * f + col[ct];
-          const int G = mx_granules(d);
-          const size_t emat = (size_t)sw.e * f * G * 8;     // the expert's scale matrix
-          wp[2 * ct] = {a.q1 + r * (d / 2) + k0 / 2, mx_row(a.e1 + emat, col[ct], G), (int)k0};
-          wp[2 * ct + 1] = {a.q3 + r * (d / 2) + k0 / 2, mx_row(a.e3 + emat, col[ct], G),
-                            (int)k0};
-        }
-      }
-      __shared__ __align__(16) uint16_t stage[Stage<U, false>::kElems];
-      __shared__ int s_tok[kStageRows];
-      const int R = min(kStageRows, te - c0);
-      if (threadIdx.x < R)
-        s_tok[threadIdx.x] =
-            sw.shared ? sw.t0 + c0 + threadIdx.x : a.perm[p0 + c0 + threadIdx.x] / a.k;
-      __syncthreads();
-      staged_pass<kW, U, false, NM, kTiles>(a.x + kbase, d, s_tok, R, wp, Kg, 0, acc, stage);
-    } else if constexpr (kW == kFp8) {
-      const uint8_t* brow[NM];
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const size_t wrow = (size_t)col[ct] * d + k0;
-        brow[2 * ct] = slot_q(a, sw, a.q1) + wrow;
-        brow[2 * ct + 1] = slot_q(a, sw, a.q3) + wrow;
-      }
-      wave_pass_q8<U, NM>(arow, nt, brow, Kg, acc);
-    } else if constexpr (kW == kMx4) {
-      // row col of the expert: d / 2 code bytes; its tiled scale row
-      const uint8_t* brow[NM];
-      const uint8_t* srow[NM];
-      const int G = mx_granules(d);
-      const size_t emat = (size_t)sw.e * f * G * 8;
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
+    for (int ct = 0; ct < CT; ++ct) {
+      const size_t wrow = (size_t)col[ct] * d + k0;
+      if constexpr (kW == kBf16) {
+        wp[2 * ct].w = slot_w(a, sw, a.w1, a.sw1) + wrow;
+        wp[2 * ct + 1].w = slot_w(a, sw, a.w3, a.sw3) + wrow;
+      } else if constexpr (kW == kFp8) {
+        wp[2 * ct].w = slot_q(a, sw, a.q1) + wrow;
+        wp[2 * ct + 1].w = slot_q(a, sw, a.q3) + wrow;
+      } else {        // row col of the expert: d / 2 code bytes; its tiled scale row
         const size_t r = (size_t)sw.e * f + col[ct];
-        brow[2 * ct] = a.q1 + r * (d / 2) + k0 / 2;
-        brow[2 * ct + 1] = a.q3 + r * (d / 2) + k0 / 2;
-        srow[2 * ct] = mx_row(a.e1 + emat, col[ct], G);
-        srow[2 * ct + 1] = mx_row(a.e3 + emat, col[ct], G);
+        const int G = mx_granules(d);
+        const size_t emat = (size_t)sw.e * f * G * 8;     // the expert's scale matrix
+        wp[2 * ct] = {a.q1 + r * (d / 2) + k0 / 2, mx_row(a.e1 + emat, col[ct], G), (int)k0};
+        wp[2 * ct + 1] = {a.q3 + r * (d / 2) + k0 / 2, mx_row(a.e3 + emat, col[ct], G), (int)k0};
       }
-      wave_pass_q4<U, NM>(arow, nt, brow, srow, (int)k0, Kg, acc);
-    } else {
-      const uint16_t* brow[NM];
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const size_t wrow = (size_t)col[ct] * d + k0;
-        brow[2 * ct] = slot_w(a, sw, a.w1, a.sw1) + wrow;
-        brow[2 * ct + 1] = slot_w(a, sw, a.w3, a.sw3) + wrow;
-      }
-      wave_pass<U, NM, XS_GATE_UP_ADBL != 0>(arow, nt, brow, Kg, acc);
     }
+    __shared__ __align__(16) uint16_t stage[Stage<U, false>::kElems];
+    __shared__ int s_tok[kStageRows];
+    const int R = min(kStageRows, te - c0);
+    if (threadIdx.x < R)
+      s_tok[threadIdx.x] =
+          sw.shared ? p0 - a.T * (a.k + sw.e) + c0 + threadIdx.x   // shared rows: token order
+                    : a.perm[p0 + c0 + threadIdx.x] / a.k;
+    __syncthreads();
+    staged_pass<kW, U, false, NM, kRest, kTiles>(a.x + kbase, d, s_tok, R, wp, Kg, 0, acc, stage);
 #pragma unroll
     for (int rt = 0; rt < kTiles; ++rt) {
       if (rt >= nt) break;
@@ -950,8 +841,8 @@ __launch_bounds__(kBlock) void gate_up_kernel(FfnArgs a) {
 // Staged down instances are held to 2 waves per SIMD: left alone the compiler took 1 for the
 // 64-row bf16 and FP8 instances (FP8 DeepSeek T=32 down 166 -> 138 us with the hint).
 // TL: token tiles per pass, 8 tokens each (hi and lo rows).
-template <int U, int kW, int NM, int TL = XS_DOWN_TL>
-__global__ __attribute__((amdgpu_waves_per_eu(stage_down(kW) && NM <= 4 ? XS_DOWN_WAVES_PER_EU
+template <int U, int kW, int NM, bool kRest, int TL = XS_DOWN_TL>
+__global__ __attribute__((amdgpu_waves_per_eu(NM <= 4 ? XS_DOWN_WAVES_PER_EU
                                                                           : 1)))
 __launch_bounds__(kBlock) void down_kernel(FfnArgs a) {
   // (bx, slot): this block's column block and expert slot.  In grids of at least
@@ -976,15 +867,12 @@ __launch_bounds__(kBlock) void down_kernel(FfnArgs a) {
   const int p0 = sw.p0, te = sw.te;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n0 = (bx * kWaves + wave) * kCols * NM;
-  // a staged pass needs the whole block (see gate_up_kernel)
-  constexpr bool kStaged = stage_down(kW);
-  if (!kStaged && n0 >= a.d) return;
+  // the staged pass needs the whole block (see gate_up_kernel)
   const int n = lane & 15, g = lane >> 4;
   const int d = a.d, f = a.f;
   const int Ks = f / a.splits;                 // this block's part of the reduction
-  const size_t k0 = (size_t)blockIdx.z * Ks + (size_t)(kW == kBf16 ? klane<U>(g) : g * 8 * U);
+  const size_t k0 = (size_t)blockIdx.z * Ks + (size_t)(kW == kBf16 ? klane(g) : g * 8 * U);
   float* const ypart = a.yslot + (size_t)blockIdx.z * a.rows * d;
-  const int lo_off = n < 8 ? 0 : 8;                    // A rows 0-7: hi, rows 8-15: lo
   size_t wrow[NM];
   int rowm[NM];
   float sc[NM];                                        // FP8 per-row scales (else 1)
@@ -997,69 +885,38 @@ __launch_bounds__(kBlock) void down_kernel(FfnArgs a) {
 
   for (int c0 = 0; c0 < te; c0 += 8 * TL) {
     const int nt = min(TL, (te - c0 + 7) / 8);
-    const uint16_t* arow[TL];
-#pragma unroll
-    for (int rt = 0; rt < TL; ++rt) {
-      const int t = min(c0 + rt * 8 + (n & 7), te - 1);
-      arow[rt] = a.h + (size_t)(p0 + t) * 2 * f + 2 * k0 + lo_off;
-    }
     floatx4 acc[NM][TL];
 #pragma unroll
     for (int m = 0; m < NM; ++m)
 #pragma unroll
       for (int rt = 0; rt < TL; ++rt) acc[m][rt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // Consecutive waves start their pass over K one step apart (and wrap around): W2 rows
-    // are f elements apart, often a power of two, so waves that stepped through K in the
+    // Consecutive blocks start their pass over K one step apart (and wrap around): W2 rows
+    // are f elements apart, often a power of two, so blocks that stepped through K in the
     // same order would read the same offsets of every row at the same time.
     const int rot = kW == kBf16 ? XS_DOWN_ROT : (kW == kFp8 ? XS_Q8_DOWN_ROT : XS_Q4_DOWN_ROT);
-    const int k_first = (int)(((bx * kWaves + wave) * rot) % (Ks / (32 * U))) * 32 * U;
-    if constexpr (kStaged) {
-      static_assert(TL == 2 || TL == 4, "the staged pass takes two or four 8-token tiles");
-      typename WTile<kW, U>::Ptr wp[NM];
+    const int k_first = kRest ? 0 : (int)((bx * rot) % (Ks / (32 * U))) * 32 * U;
+    static_assert(TL == 2 || TL == 4, "two or four 8-token tiles");
+    typename WTile<kW, U>::Ptr wp[NM];
 #pragma unroll
-      for (int m = 0; m < NM; ++m) {
-        if constexpr (kW == kBf16) {
-          wp[m].w = slot_w(a, sw, a.w2, a.sw2) + wrow[m];
-        } else if constexpr (kW == kFp8) {
-          wp[m].w = slot_q(a, sw, a.q2) + wrow[m];
-        } else {         // f / 2 code bytes of row rowm; its tiled scale row
-          const size_t r = (size_t)sw.e * d + rowm[m];
-          const int G = mx_granules(f);
-          wp[m] = {a.q2 + r * (f / 2) + k0 / 2,
-                   mx_row(a.e2 + (size_t)sw.e * d * G * 8, rowm[m], G), (int)k0};
-        }
+    for (int m = 0; m < NM; ++m) {
+      if constexpr (kW == kBf16) {
+        wp[m].w = slot_w(a, sw, a.w2, a.sw2) + wrow[m];
+      } else if constexpr (kW == kFp8) {
+        wp[m].w = slot_q(a, sw, a.q2) + wrow[m];
+      } else {         // f / 2 code bytes of row rowm; its tiled scale row
+        const size_t r = (size_t)sw.e * d + rowm[m];
+        const int G = mx_granules(f);
+        wp[m] = {a.q2 + r * (f / 2) + k0 / 2,
+                 mx_row(a.e2 + (size_t)sw.e * d * G * 8, rowm[m], G), (int)k0};
       }
-      __shared__ __align__(16) uint16_t stage[Stage<U, true>::kElems];
-      __shared__ int s_tok[kStageRows];
-      const int R = min(8 * TL, te - c0);
-      if (threadIdx.x < R) s_tok[threadIdx.x] = p0 + c0 + threadIdx.x;   // H rows
-      __syncthreads();
-      // staged: consecutive blocks, not waves, start their pass `rot` steps apart
-      const int kb_first = (int)((bx * rot) % (Ks / (32 * U))) * 32 * U;
-      staged_pass<kW, U, true, NM, TL>(a.h + 2 * (size_t)blockIdx.z * Ks, 2 * (size_t)f, s_tok, R,
-                                       wp, Ks, kb_first, acc, stage);
-    } else if constexpr (kW == kFp8) {
-      const uint8_t* brow[NM];
-#pragma unroll
-      for (int m = 0; m < NM; ++m) brow[m] = slot_q(a, sw, a.q2) + wrow[m];
-      wave_pass_q8<U, NM, TL, 2>(arow, nt, brow, Ks, acc, k_first);
-    } else if constexpr (kW == kMx4) {
-      const uint8_t* brow[NM];
-      const uint8_t* srow[NM];
-      const int G = mx_granules(f);
-#pragma unroll
-      for (int m = 0; m < NM; ++m) {
-        const size_t r = (size_t)sw.e * d + rowm[m];      // f / 2 code bytes; tiled scale row
-        brow[m] = a.q2 + r * (f / 2) + k0 / 2;
-        srow[m] = mx_row(a.e2 + (size_t)sw.e * d * G * 8, rowm[m], G);
-      }
-      wave_pass_q4<U, NM, TL, 2>(arow, nt, brow, srow, (int)k0, Ks, acc, k_first);
-    } else {
-      const uint16_t* brow[NM];
-#pragma unroll
-      for (int m = 0; m < NM; ++m) brow[m] = slot_w(a, sw, a.w2, a.sw2) + wrow[m];
-      wave_pass<U, NM, XS_DOWN_ADBL != 0, TL, 2>(arow, nt, brow, Ks, acc, k_first);
     }
+    __shared__ __align__(16) uint16_t stage[Stage<U, true>::kElems];
+    __shared__ int s_tok[kStageRows];
+    const int R = min(8 * TL, te - c0);
+    if (threadIdx.x < R) s_tok[threadIdx.x] = p0 + c0 + threadIdx.x;   // H rows
+    __syncthreads();
+    staged_pass<kW, U, true, NM, kRest, TL>(a.h + 2 * (size_t)blockIdx.z * Ks, 2 * (size_t)f,
+                                            s_tok, R, wp, Ks, k_first, acc, stage);
 #pragma unroll
     for (int rt = 0; rt < TL; ++rt) {
       if (rt >= nt) break;
@@ -1178,7 +1035,7 @@ __launch_bounds__(kBlock) void down_seq_kernel(FfnArgs a) {
   const bool xcd = a.max_active + a.shared_slots >= XS_DOWN_XCD_SLOTS;
   const int nsteps = f / KB;                    // unsplit: the launch takes one K part
   const int rot = kW == kBf16 ? XS_DOWN_ROT : XS_Q8_DOWN_ROT;
-  const size_t kl = (size_t)(kW == kBf16 ? klane<U>(g) : g * 8 * U);
+  const size_t kl = (size_t)(kW == kBf16 ? klane(g) : g * 8 * U);
 
   // the block's unit records, one thread each
   __shared__ int4 s_rec[kSeqUnits];
@@ -1461,8 +1318,8 @@ __global__ __launch_bounds__(kBlock) void router_kernel(RouterArgs r) {
   if (j0 >= r.N) return;
   const int n = lane & 15, g = lane >> 4;
   const int Kp = r.d / r.parts;
-  const size_t k0 = (size_t)blockIdx.z * Kp + (size_t)klane<U>(g);
-  const uint16_t* const brow[1] = {r.wg + (size_t)min(j0 + n, r.N - 1) * r.d + k0};
+  const size_t k0 = (size_t)blockIdx.z * Kp + (size_t)klane(g);
+  const uint16_t* const brow = r.wg + (size_t)min(j0 + n, r.N - 1) * r.d + k0;
   float* const out = r.planes + (size_t)blockIdx.z * r.T * r.N;
   for (int c0 = blockIdx.y * 16 * kTiles; c0 < r.T; c0 += gridDim.y * 16 * kTiles) {
     const int nt = min(kTiles, (r.T - c0 + 15) / 16);
@@ -1470,17 +1327,17 @@ __global__ __launch_bounds__(kBlock) void router_kernel(RouterArgs r) {
 #pragma unroll
     for (int rt = 0; rt < kTiles; ++rt)
       arow[rt] = r.x + (size_t)min(c0 + rt * 16 + n, r.T - 1) * r.d + k0;
-    floatx4 acc[1][kTiles];
+    floatx4 acc[kTiles];
 #pragma unroll
-    for (int rt = 0; rt < kTiles; ++rt) acc[0][rt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    wave_pass<U, 1, true>(arow, nt, brow, Kp, acc);
+    for (int rt = 0; rt < kTiles; ++rt) acc[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    wave_pass<U>(arow, nt, brow, Kp, acc);
 #pragma unroll
     for (int rt = 0; rt < kTiles; ++rt) {
       if (rt >= nt) break;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int t = c0 + rt * 16 + 4 * g + i;
-        if (t < r.T && j0 + n < r.N) out[(size_t)t * r.N + j0 + n] = acc[0][rt][i];
+        if (t < r.T && j0 + n < r.N) out[(size_t)t * r.N + j0 + n] = acc[rt][i];
       }
     }
   }
@@ -1504,8 +1361,6 @@ __global__ __launch_bounds__(kBlock) void router_sum_kernel(RouterArgs r) {
   r.logits[idx] = v;
 }
 
-int unroll_for(int K, int want);
-
 // Column tiles per wave: two if the expected active blocks stay enough with them.
 bool gu_two_tiles(const FfnArgs& a, int kW, unsigned splits) {
   const long min_blocks = kW == kMx4 ? XS_Q4_GU_CT2_MIN_BLOCKS : XS_GU_CT2_MIN_BLOCKS;
@@ -1513,18 +1368,17 @@ bool gu_two_tiles(const FfnArgs& a, int kW, unsigned splits) {
              (a.est_active + a.shared_slots) * splits >= min_blocks;
 }
 
-// Blocks of the unsplit gate/up instance the GPU runs at once (cached per instance; one
-// device type).
-template <int U, int kW, int CT>
-int resident_blocks() {
-  static std::atomic<int> cached{0};   // callers on several threads may fill it at once
+// Blocks of the kernel that the GPU runs at once (0: unknown).  The callers keep the figure in
+// `cached`, one per instance (one device type; callers on several threads may fill it at once).
+template <typename K>
+int resident_blocks(K kernel, std::atomic<int>& cached) {
   int r = cached.load(std::memory_order_relaxed);
   if (r == 0) {
     int per_cu = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gate_up_kernel<U, false, kW, CT>,
-                                                     kBlock, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, 0) != hipSuccess ||
         hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        per_cu <= 0)
       return 0;
     r = per_cu * cus;
     cached.store(r, std::memory_order_relaxed);
@@ -1565,104 +1419,68 @@ void launch_gu_tail(const FfnArgs& a, dim3 grid, int s_main, int ts, hipStream_t
   t.part_compact = 1;
   const int tail = (int)grid.y - s_main;
   const dim3 g(grid.x, tail, ts), block(kBlock);
-  hipLaunchKernelGGL((gate_up_kernel<U, true, kW, CT>), g, block, 0, stream, t);
+  hipLaunchKernelGGL((gate_up_kernel<U, true, kW, CT, false>), g, block, 0, stream, t);
   const dim3 fg((a.f + kBlock * 4 - 1) / (kBlock * 4), tail * a.T);
   hipLaunchKernelGGL(gate_up_tail_finish_kernel, fg, block, 0, stream, t);
 }
 
-// An unsplit launch, with its last round's slots split off when that pays (see
-// gu_tail_split).
-template <int U, int kW, int CT>
-void launch_gu_unsplit(const FfnArgs& a, dim3 grid, dim3 block, hipStream_t stream) {
-  int s_main = 0;
-  const int ts = gu_tail_split<U>(a, grid, resident_blocks<U, kW, CT>(), s_main);
-  const dim3 g(grid.x, s_main, grid.z);
-  if (s_main > 0) hipLaunchKernelGGL((gate_up_kernel<U, false, kW, CT>), g, block, 0, stream, a);
-  if (ts > 1) launch_gu_tail<U, kW, CT>(a, grid, s_main, ts, stream);
+// The gate/up launch of one instance; an unsplit one with its last round's slots split off when
+// that pays (see gu_tail_split; its parts are whole steps).
+template <int U, int kW, int CT, bool kRest>
+void launch_gu(const FfnArgs& a, dim3 grid, hipStream_t stream) {
+  const dim3 block(kBlock);
+  grid.x = (a.f + CT * kWaves * kCols - 1) / (CT * kWaves * kCols);
+  if (grid.z > 1) {
+    hipLaunchKernelGGL((gate_up_kernel<U, true, kW, CT, kRest>), grid, block, 0, stream, a);
+    return;
+  }
+  int s_main = (int)grid.y, ts = 1;
+  if constexpr (!kRest) {
+    static std::atomic<int> resident{0};
+    ts = gu_tail_split<U>(
+        a, grid, resident_blocks(gate_up_kernel<U, false, kW, CT, false>, resident), s_main);
+  }
+  if (s_main > 0)
+    hipLaunchKernelGGL((gate_up_kernel<U, false, kW, CT, kRest>), dim3(grid.x, s_main, 1), block, 0,
+                       stream, a);
+  if constexpr (!kRest)
+    if (ts > 1) launch_gu_tail<U, kW, CT>(a, grid, s_main, ts, stream);
 }
 
-template <int U, int kW>
-void launch_gu(const FfnArgs& a, bool split, bool two, dim3 grid, dim3 block,
-               hipStream_t stream) {
-  if (two) grid.x = (a.f + 2 * kWaves * kCols - 1) / (2 * kWaves * kCols);
-  if constexpr (U <= 8) {   // U = 16: one-tile launches only
-    if (split && two) {
-      hipLaunchKernelGGL((gate_up_kernel<U, true, kW, 2>), grid, block, 0, stream, a);
-      return;
-    }
-    if (two) {
-      launch_gu_unsplit<U, kW, 2>(a, grid, block, stream);
-      return;
-    }
+// Step of the launches over reductions that are no multiple of the format's own: half of it for
+// MXFP4 (its 8-word partial step spilled 80 registers), else the same.
+template <int kW, int U>
+constexpr int rest_step() { return kW == kMx4 && U == 8 ? 4 : U; }
+
+// U2 / U1: steps of two-tile and of one-tile launches for weight format kW, over reductions of K.
+template <int kW, int U2, int U1>
+void launch_gu_fmt(const FfnArgs& a, int K, dim3 grid, hipStream_t stream) {
+  if (gu_two_tiles(a, kW, grid.z)) {
+    if (K % (32 * U2) == 0) launch_gu<U2, kW, 2, false>(a, grid, stream);
+    else launch_gu<rest_step<kW, U2>(), kW, 2, true>(a, grid, stream);
+  } else {
+    if (K % (32 * U1) == 0) launch_gu<U1, kW, 1, false>(a, grid, stream);
+    else launch_gu<rest_step<kW, U1>(), kW, 1, true>(a, grid, stream);
   }
-  if (split)
-    hipLaunchKernelGGL((gate_up_kernel<U, true, kW, 1>), grid, block, 0, stream, a);
-  else
-    launch_gu_unsplit<U, kW, 1>(a, grid, block, stream);
 }
 
-// Unroll U (a power of two dividing K / 32; at most u2 for two-tile launches, u1 for
-// one-tile launches, 16 only for MXFP4) for weight format kW.
-template <int kW>
-void launch_gu_fmt(const FfnArgs& a, int K, int u2, int u1, bool split, dim3 grid, dim3 block,
-                   hipStream_t stream) {
-  const bool two = gu_two_tiles(a, kW, grid.z);
-  const int u = unroll_for(K, two ? u2 : u1);
-  if constexpr (kW == kMx4 && (XS_Q4_GATE_UP_U == 16 || XS_Q4_GATE_UP_U1 == 16)) {
-    if (u == 16) {
-      launch_gu<16, kW>(a, split, false, grid, block, stream);
-      return;
-    }
-  }
-  if (u >= 8)
-    launch_gu<8, kW>(a, split, two, grid, block, stream);
-  else if (u == 4)
-    launch_gu<4, kW>(a, split, two, grid, block, stream);
-  else if (u == 2)
-    launch_gu<2, kW>(a, split, two, grid, block, stream);
-  else
-    launch_gu<1, kW>(a, split, two, grid, block, stream);
-}
-// Blocks of the down instance (unroll u) that the GPU runs at once (cached per instance).
-template <int U, int kW, int NM, int TL>
-int down_resident_u() {
+// Blocks of a down instance that the GPU runs at once.
+template <int U, int kW, int NM, bool kRest, int TL = XS_DOWN_TL>
+int down_resident() {
   static std::atomic<int> cached{0};
-  int r = cached.load(std::memory_order_relaxed);
-  if (r == 0) {
-    int per_cu = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, down_kernel<U, kW, NM, TL>, kBlock,
-                                                     0) != hipSuccess ||
-        hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      return 0;
-    r = per_cu * cus;
-    cached.store(r, std::memory_order_relaxed);
-  }
-  return r;
-}
-template <int kW, int NM, int TL = XS_DOWN_TL>
-int down_resident(int u) {
-  if (u == 8) return down_resident_u<8, kW, NM, TL>();
-  if (u >= 4) return down_resident_u<4, kW, NM, TL>();
-  if (u == 2) return down_resident_u<2, kW, NM, TL>();
-  return down_resident_u<1, kW, NM, TL>();
+  return resident_blocks(down_kernel<U, kW, NM, kRest, TL>, cached);
 }
 
-template <int kW, int NM, int TL = XS_DOWN_TL>
-void launch_down_fmt(const FfnArgs& a, int u, hipStream_t stream) {
+template <int U, int kW, int NM, int TL = XS_DOWN_TL>
+void launch_down_fmt(const FfnArgs& a, hipStream_t stream) {
   const int cols = kWaves * kCols * NM;
   const int slots = a.max_active + a.shared_slots;
   const dim3 grid((a.d + cols - 1) / cols, slots, a.splits), block(kBlock);
-  if (u == 8) {
-    hipLaunchKernelGGL((down_kernel<8, kW, NM, TL>), grid, block, 0, stream, a);
-    return;
-  }
-  if (u >= 4)
-    hipLaunchKernelGGL((down_kernel<4, kW, NM, TL>), grid, block, 0, stream, a);
-  else if (u == 2)
-    hipLaunchKernelGGL((down_kernel<2, kW, NM, TL>), grid, block, 0, stream, a);
+  if ((a.f / a.splits) % (32 * U) == 0)
+    hipLaunchKernelGGL((down_kernel<U, kW, NM, false, TL>), grid, block, 0, stream, a);
   else
-    hipLaunchKernelGGL((down_kernel<1, kW, NM, TL>), grid, block, 0, stream, a);
+    hipLaunchKernelGGL((down_kernel<rest_step<kW, U>(), kW, NM, true, TL>), grid, block, 0, stream,
+                       a);
 }
 
 // The persistent down launch (down_seq_kernel): one block per resident slot, rounded up to a
@@ -1671,18 +1489,8 @@ void launch_down_fmt(const FfnArgs& a, int u, hipStream_t stream) {
 template <int U, int kW, int NM, int TL = XS_DOWN_TL>
 bool launch_down_seq(const FfnArgs& a, hipStream_t stream) {
   static std::atomic<int> cached{0};
-  int r = cached.load(std::memory_order_relaxed);
-  if (r == 0) {
-    int per_cu = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, down_seq_kernel<U, kW, NM, TL>,
-                                                     kBlock, 0) != hipSuccess ||
-        hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        per_cu <= 0)
-      return false;
-    r = per_cu * cus;
-    cached.store(r, std::memory_order_relaxed);
-  }
+  const int r = resident_blocks(down_seq_kernel<U, kW, NM, TL>, cached);
+  if (r == 0) return false;
   const int CB = (a.d + kWaves * kCols * NM - 1) / (kWaves * kCols * NM);
   const long max_units = (long)(a.max_active + a.shared_slots) * CB;
   long G = std::max<long>(r, (max_units + kSeqUnits - 1) / kSeqUnits);
@@ -1692,27 +1500,20 @@ bool launch_down_seq(const FfnArgs& a, hipStream_t stream) {
   return true;
 }
 
-int unroll_for(int K, int want) {
-  for (int u = want; u > 1; u >>= 1)
-    if (K % (32 * u) == 0) return u;
-  return 1;
-}
-
 }  // namespace
 
 hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
   const int cols = kWaves * kCols;            // one column tile per wave; launch_gu may take two
   const dim3 grid((a.f + cols - 1) / cols, a.max_active + a.shared_slots, a.gu_splits),
       block(kBlock);
-  const bool split = a.gu_splits > 1;
   const int K = a.d / a.gu_splits;
   if (a.wfmt == kFp8)
-    launch_gu_fmt<kFp8>(a, K, XS_Q8_GATE_UP_U, XS_Q8_GATE_UP_U1, split, grid, block, stream);
+    launch_gu_fmt<kFp8, XS_Q8_GATE_UP_U, XS_Q8_GATE_UP_U1>(a, K, grid, stream);
   else if (a.wfmt == kMx4)
-    launch_gu_fmt<kMx4>(a, K, XS_Q4_GATE_UP_U, XS_Q4_GATE_UP_U1, split, grid, block, stream);
+    launch_gu_fmt<kMx4, XS_Q4_GATE_UP_U, XS_Q4_GATE_UP_U1>(a, K, grid, stream);
   else
-    launch_gu_fmt<kBf16>(a, K, XS_GATE_UP_U, XS_GATE_UP_U1, split, grid, block, stream);
-  if (split) {
+    launch_gu_fmt<kBf16, XS_GATE_UP_U, XS_GATE_UP_U1>(a, K, grid, stream);
+  if (a.gu_splits > 1) {
     const dim3 fgrid((a.f + kBlock * 4 - 1) / (kBlock * 4), (unsigned)std::min(a.rows, 65535L));
     hipLaunchKernelGGL(gate_up_finish_kernel, fgrid, block, 0, stream, a);
   }
@@ -1731,9 +1532,9 @@ hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
     const bool wide = XS_Q4_DN_WIDE && est > 0 && (long)a.T * a.k <= 8 * est &&
                       (long)((a.d + wcols - 1) / wcols) * est * a.splits >= XS_DN_WIDE_MIN_BLOCKS;
     if (wide)
-      launch_down_fmt<kMx4, 2 * XS_Q4_DOWN_NM, 2>(a, unroll_for(K, XS_Q4_DOWN_U), stream);
+      launch_down_fmt<XS_Q4_DOWN_U, kMx4, 2 * XS_Q4_DOWN_NM, 2>(a, stream);
     else
-      launch_down_fmt<kMx4, XS_Q4_DOWN_NM>(a, unroll_for(K, XS_Q4_DOWN_U), stream);
+      launch_down_fmt<XS_Q4_DOWN_U, kMx4, XS_Q4_DOWN_NM>(a, stream);
     return hipGetLastError();
   }
   // bf16 and FP8: twice the rows per wave (one token load feeding twice the weight tiles)
@@ -1747,9 +1548,8 @@ hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
   bool wide = est > 0 && (long)a.T * a.k >= XS_DN_WIDE_TOKENS * est &&
               wide_blocks >= XS_DN_WIDE_MIN_BLOCKS;
   if (!wide && est > 0 && (long)a.T * a.k >= XS_DN_WIDE_TOKENS * est) {
-    const int r = a.wfmt == kFp8
-                      ? down_resident<kFp8, 2 * XS_Q8_DOWN_NM>(unroll_for(K, XS_Q8_DOWN_U))
-                      : down_resident<kBf16, 2 * XS_DOWN_NM>(unroll_for(K, XS_DOWN_U));
+    const int r = a.wfmt == kFp8 ? down_resident<XS_Q8_DOWN_U, kFp8, 2 * XS_Q8_DOWN_NM, false>()
+                                 : down_resident<XS_DOWN_U, kBf16, 2 * XS_DOWN_NM, false>();
     wide = r > 0 && wide_blocks >= r && wide_blocks % r == 0;
   }
 #if XS_DOWN_NM7
@@ -1757,31 +1557,30 @@ hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
   // for one GPU group's share, whose expected count (the group's experts under plain top-k)
   // overstates its live slots: the plain top-k share of DeepSeek T=32 (about 12 live of 32
   // slots) ran down 296 us with 64-row waves and 324 us with seven tiles
-  if (a.wfmt == kBf16 && est > 0 && a.local_group < 0 &&
+  if (a.wfmt == kBf16 && est > 0 && a.local_group < 0 && K % (32 * XS_DOWN_NM7_U) == 0 &&
       (long)a.T * a.k >= XS_DN_WIDE_TOKENS * est) {
     const long b7 = (long)((a.d + kWaves * kCols * 7 - 1) / (kWaves * kCols * 7)) * est * a.splits;
-    const int u7 = unroll_for(K, XS_DOWN_NM7_U);
-    const int r7 = down_resident<kBf16, 7>(u7);
+    const int r7 = down_resident<XS_DOWN_NM7_U, kBf16, 7, false>();
     if (r7 > 0 && b7 >= r7 && b7 % r7 == 0) {
 #if XS_DOWN_SEQ
-      if (a.splits == 1 && u7 == 4 && launch_down_seq<4, kBf16, 7>(a, stream))
+      if (a.splits == 1 && launch_down_seq<XS_DOWN_NM7_U, kBf16, 7>(a, stream))
         return hipGetLastError();
 #endif
-      launch_down_fmt<kBf16, 7>(a, u7, stream);
+      launch_down_fmt<XS_DOWN_NM7_U, kBf16, 7>(a, stream);
       return hipGetLastError();
     }
   }
 #endif
   if (a.wfmt == kFp8) {
     if (wide)
-      launch_down_fmt<kFp8, 2 * XS_Q8_DOWN_NM>(a, unroll_for(K, XS_Q8_DOWN_U), stream);
+      launch_down_fmt<XS_Q8_DOWN_U, kFp8, 2 * XS_Q8_DOWN_NM>(a, stream);
     else
-      launch_down_fmt<kFp8, XS_Q8_DOWN_NM>(a, unroll_for(K, XS_Q8_DOWN_U), stream);
+      launch_down_fmt<XS_Q8_DOWN_U, kFp8, XS_Q8_DOWN_NM>(a, stream);
   } else {
     if (wide)
-      launch_down_fmt<kBf16, 2 * XS_DOWN_NM>(a, unroll_for(K, XS_DOWN_U), stream);
+      launch_down_fmt<XS_DOWN_U, kBf16, 2 * XS_DOWN_NM>(a, stream);
     else
-      launch_down_fmt<kBf16, XS_DOWN_NM>(a, unroll_for(K, XS_DOWN_U), stream);
+      launch_down_fmt<XS_DOWN_U, kBf16, XS_DOWN_NM>(a, stream);
   }
   return hipGetLastError();
 }
@@ -1790,11 +1589,10 @@ hipError_t launch_router(const RouterArgs& r, hipStream_t stream) {
   const dim3 grid((r.N + kWaves * kCols - 1) / (kWaves * kCols), router_token_groups(r.T),
                   r.parts),
       block(kBlock);
-  switch (unroll_for(r.d / r.parts, 4)) {
-    case 4: hipLaunchKernelGGL(router_kernel<4>, grid, block, 0, stream, r); break;
-    case 2: hipLaunchKernelGGL(router_kernel<2>, grid, block, 0, stream, r); break;
-    default: hipLaunchKernelGGL(router_kernel<1>, grid, block, 0, stream, r); break;
-  }
+  const int K = r.d / r.parts;
+  if (K % 128 == 0) hipLaunchKernelGGL(router_kernel<4>, grid, block, 0, stream, r);
+  else if (K % 64 == 0) hipLaunchKernelGGL(router_kernel<2>, grid, block, 0, stream, r);
+  else hipLaunchKernelGGL(router_kernel<1>, grid, block, 0, stream, r);
   const size_t n = (size_t)r.T * r.N;
   hipLaunchKernelGGL(router_sum_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), block, 0,
                      stream, r);

@@ -280,7 +280,8 @@ struct FfnArgs {
   int T, N, k, d, f;
   int max_active;              // host bound on the routed expert slots (grid size)
   int est_active;              // routed expert slots expected (0: unknown), for launch shapes
-  int shared_slots;            // slots of the shared experts: n_shared * ceil(T / kSlotRows)
+  int shared_parts;            // slots of one shared expert: ceil(T / kSlotRows)
+  int shared_slots;            // slots of the shared experts: n_shared * shared_parts
   int splits;                  // K-splits of the down GEMM (partials summed in the combine)
   int gu_splits;               // K-splits of the gate/up GEMM (partials summed by finish)
   float* gpart;                // [gu_splits, 2, part_rows, f] when gu_splits > 1 (or the tail's)
