@@ -5,7 +5,7 @@
 Translation units:
 * route.hip -- expert selection; -ffp-contract=off and correctly rounded fp32 division, so
                the gate arithmetic is exactly the documented sequence of fp32 operations;
-* ffn.hip   -- expert GEMMs (bf16 MFMA) and the combine;
+* ffn.hip   -- expert GEMMs (bf16 MFMA) and the combine (ffn_wide.h: those of large batches);
 * abi.hip   -- the extern "C" entry points declared in include/xshare.h;
 * probe.hip -- the streaming-read probe (measurement of the HBM read ceiling).
 Every HIP compile disables packed-fp32 instruction selection.  The same sources built with

@@ -355,8 +355,8 @@ struct WTile<kMx4, U> {
   struct Ptr { const uint8_t* w; const uint8_t* sc; int k; };
   // scale bytes (block u / 4 in byte u / 4) in a type no wider than their load: a widening
   // at the end of a step would wait for the load
-  using E = typename std::conditional<(U > 8), uint32_t,
-                                      typename std::conditional<(U == 8), uint16_t, uint8_t>::type>::type;
+  using E8 = typename std::conditional<(U == 8), uint16_t, uint8_t>::type;
+  using E = typename std::conditional<(U > 8), uint32_t, E8>::type;
   struct Regs { Q4<U> q; E e; };
   struct Rest { uint32_t w[U]; uint8_t e[U]; };
   __device__ static constexpr int koff(int g, int u) { return 8 * U * g + 8 * u; }
@@ -439,7 +439,8 @@ __device__ __forceinline__ void block_pass(const uint16_t* x, size_t ld, const i
       const int ka = S::AS * (32 * u + 8 * g);
       bf16x8 xa[NT];
 #pragma unroll
-      for (int rt = 0; rt < NT; ++rt) xa[rt] = *reinterpret_cast<const bf16x8*>(cur + rofs[rt] + ka);
+      for (int rt = 0; rt < NT; ++rt)
+        xa[rt] = *reinterpret_cast<const bf16x8*>(cur + rofs[rt] + ka);
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
         const bf16x8 bv = WT::operand_rest(rb[kRest ? m : 0], u);
@@ -472,7 +473,8 @@ __device__ __forceinline__ void block_pass(const uint16_t* x, size_t ld, const i
       const int ka = S::AS * WT::koff(g, u);
       bf16x8 xa[NT];
 #pragma unroll
-      for (int rt = 0; rt < NT; ++rt) xa[rt] = *reinterpret_cast<const bf16x8*>(cur + rofs[rt] + ka);
+      for (int rt = 0; rt < NT; ++rt)
+        xa[rt] = *reinterpret_cast<const bf16x8*>(cur + rofs[rt] + ka);
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
         const bf16x8 bv = WT::operand(b[m], u);
@@ -1189,6 +1191,8 @@ __launch_bounds__(kBlock) void down_seq_kernel(FfnArgs a) {
   }
 }
 
+#include "ffn_wide.h"
+
 // Sums the gate and up partials of hidden element c..c+3 of partial row `prow` in split
 // order, then H[hrow] = silu(gate) * up as bf16 hi and lo.
 __device__ __forceinline__ void finish_row(const FfnArgs& a, size_t prow, size_t hrow, int c) {
@@ -1500,6 +1504,47 @@ bool launch_down_seq(const FfnArgs& a, hipStream_t stream) {
   return true;
 }
 
+// Launches for large batches (ffn_wide.h) where an expert holds 16 rows or more on average (24
+// with MXFP4; 20 with bf16 up to 64 tokens) and the batch can give one more than 32, the rows of
+// a pass of the staged launches.  Same-box A/B, layer us against the staged launches (changes of
+// gate/up and down added): bf16 DeepSeek T=96 12 rows an expert +33 of 1009, T=128 16 rows -105
+// of 1167, T=64 21 rows -98 of 512, Qwen T=64 16 rows -4 of 90; FP8 DeepSeek T=96 12 rows -16 of
+// 572, T=64 16 rows -62 of 368, Qwen T=128 16 rows -14 of 112; MXFP4 DeepSeek T=128 16 rows +60
+// of 411, 21 rows +18 of 359, T=256 26 rows -63 of 687, Qwen T=256 32 rows -15 of 127.
+bool wide_batch(const FfnArgs& a) {
+  if (a.T <= kStageRows) return false;
+  // a group's share is expected to hold its part of the routed rows
+  const long rows = (long)a.T * a.k / (a.local_group >= 0 ? a.G : 1) + (long)a.n_shared * a.T;
+  const long experts = (a.est_active > 0 ? a.est_active : a.max_active) + a.n_shared;
+  return rows >= (a.wfmt == kMx4 ? 24 : a.wfmt == kBf16 && a.T <= 64 ? 20 : 16) * experts;
+}
+
+// Gate/up with 256 weight rows a block where that leaves at least 1024 blocks (bf16) or 512 (FP8
+// and MXFP4, whose steps are twice as long then), else 128 (two blocks a CU).  256 against 128
+// rows, layer us: bf16 Mixtral T=40 (560 blocks of 256) 427 / 390, DeepSeek T=64 M=24 (384) 476 / 461,
+// T=512 (1600) 2300 / 2317; FP8 DeepSeek T=64 M=32 (512) 331 / 348, a group share (128) 155 / 147;
+// MXFP4 Qwen T=256 (384) 128 / 121, DeepSeek T=256 M=64 (1024) 571 / 642.
+template <int kW>
+void launch_gu_wide(const FfnArgs& a, hipStream_t stream) {
+  const unsigned slots = a.max_active + a.shared_slots;
+  const long est = (a.est_active > 0 ? a.est_active : a.max_active) + a.shared_slots;
+  const unsigned b256 = (a.f + 127) / 128, b128 = (a.f + 63) / 64;
+  if ((long)b256 * est * a.gu_splits >= (kW == kBf16 ? 1024 : 512))
+    hipLaunchKernelGGL((gate_up_wide_kernel<kW, 256>), dim3(b256, slots, a.gu_splits), dim3(512), 0,
+                       stream, a);
+  else
+    hipLaunchKernelGGL((gate_up_wide_kernel<kW, 128>), dim3(b128, slots, a.gu_splits), dim3(256), 0,
+                       stream, a);
+}
+// Down always with 256 rows: with 128 DeepSeek T=256 FP8 ran 1007 us a layer against 942, Mixtral
+// T=1024 3112 against 2966, the Qwen shape at T=256 117 against 120.
+template <int kW>
+void launch_dn_wide(const FfnArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL((down_wide_kernel<kW, 256>),
+                     dim3((a.d + 255) / 256, a.max_active + a.shared_slots, a.splits), dim3(512), 0,
+                     stream, a);
+}
+
 }  // namespace
 
 hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
@@ -1507,7 +1552,11 @@ hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
   const dim3 grid((a.f + cols - 1) / cols, a.max_active + a.shared_slots, a.gu_splits),
       block(kBlock);
   const int K = a.d / a.gu_splits;
-  if (a.wfmt == kFp8)
+  if (wide_batch(a)) {
+    if (a.wfmt == kFp8) launch_gu_wide<kFp8>(a, stream);
+    else if (a.wfmt == kMx4) launch_gu_wide<kMx4>(a, stream);
+    else launch_gu_wide<kBf16>(a, stream);
+  } else if (a.wfmt == kFp8)
     launch_gu_fmt<kFp8, XS_Q8_GATE_UP_U, XS_Q8_GATE_UP_U1>(a, K, grid, stream);
   else if (a.wfmt == kMx4)
     launch_gu_fmt<kMx4, XS_Q4_GATE_UP_U, XS_Q4_GATE_UP_U1>(a, K, grid, stream);
@@ -1523,6 +1572,12 @@ hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
 hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
   const int K = a.f / a.splits;
   const long est = a.est_active + a.shared_slots;
+  if (wide_batch(a)) {
+    if (a.wfmt == kFp8) launch_dn_wide<kFp8>(a, stream);
+    else if (a.wfmt == kMx4) launch_dn_wide<kMx4>(a, stream);
+    else launch_dn_wide<kBf16>(a, stream);
+    return hipGetLastError();
+  }
   if (a.wfmt == kMx4) {
     // twice the rows per wave (twice the weight bytes in flight) over 16-token passes, when
     // experts hold 8 rows or fewer on average (an expert past 16 rows reads its weights

@@ -35,7 +35,8 @@ struct RouteLayout {
   size_t offsets;   // int32 [N + 1]   exclusive prefix of tokens per expert (permuted order)
   size_t perm;      // int32 [T * k]   slot (i * k + r) of each permuted row
   size_t active;    // int4 [N + slot_extra]  expert slots: {expert, first permuted row, rows,
-                    //                 0}, so a GEMM block finds its work in one load
+                    //                 (slots of the expert - 1) << 16 | index of this one},
+                    //                 so a GEMM block finds its work in one load
   size_t counters;  // int32 [kCntCount]
   size_t dense;     // fp32 [T * N]    dense gates (score_mode DENSE only)
   size_t ids;       // int32 [T * k]   refined ids when the caller passes none

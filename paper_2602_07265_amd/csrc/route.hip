@@ -1468,7 +1468,7 @@ __global__ __launch_bounds__(kThreads) void route_lists_kernel(RouteArgs a) {
     if (listed) {
       for (int c = 0; c < parts; ++c) {
         const int lo = cnt * c / parts, hi = cnt * (c + 1) / parts;
-        a.active[at + c] = make_int4(j, off + lo, hi - lo, 0);
+        a.active[at + c] = make_int4(j, off + lo, hi - lo, (parts - 1) << 16 | c);
       }
     }
     block_excl_scan(listed ? 1 : 0, s_wsum, total);     // total: the active experts

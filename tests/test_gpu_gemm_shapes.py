@@ -1,7 +1,9 @@
 """The expert GEMMs at the edges of their launches, in every weight format, against the float64
 oracle: reductions with a partial last step (and shorter than one step), under one- and
-two-tile gate/up launches and narrow and wide down launches."""
+two-tile gate/up launches and narrow and wide down launches, and the launches of large batches
+at every count of token tiles, with experts in several slots, shared experts and GPU groups."""
 import pytest
+import torch
 
 import test_gpu_ffn
 import test_gpu_fp8
@@ -32,3 +34,44 @@ def test_partial_steps(fmt, d, f):
 def test_partial_steps_wide_launches(fmt):
     _case(fmt, 40, 120, 16, 288, 928, 110, "two tiles")
     _case(fmt, 40, 120, 16, 1760, 160, 110, "wide down")
+
+
+# two experts hold every token: T rows each (past 128 in slots of nearly equal size), for each
+# count of token tiles; d and f around the large-batch launches' steps and pairs of steps
+@FORMATS
+@pytest.mark.parametrize("T,d,f", [(33, 32, 96), (48, 64, 160), (64, 96, 32), (65, 160, 288),
+                                   (96, 128, 128), (97, 224, 416), (128, 256, 544),
+                                   (129, 288, 192), (300, 544, 352), (1000, 160, 96)])
+def test_large_batch_tiles(fmt, T, d, f):
+    _case(fmt, T, 2, 2, d, f, 2, "tiles")
+
+
+# experts of 1 to 128 rows side by side; 256 weight rows a gate/up block (2048 blocks and more)
+@FORMATS
+def test_large_batch_uneven_experts(fmt):
+    _case(fmt, 130, 64, 16, 160, 4128, 60, "uneven")
+    _case(fmt, 400, 12, 2, 608, 224, 12, "uneven")
+
+
+@pytest.mark.parametrize("T", [40, 129, 260])
+def test_large_batch_shared_experts(T):
+    import workloads as W
+    from helpers import DEV, OracleOutputs, assert_ffn_close, bf16_weights_of, make_layer, say
+    from oracle import ffn as OF
+    from paper_2602_07265_amd import xshare as X
+    c = dict(N=6, k=3, d=224, f=160, T=T, logits="domains", Q=2)
+    h, _, x, w1, w3, w2 = make_layer(c, 1)
+    sh = W.expert_weights(2, c["d"], c["f"], 9, DEV)
+    say(f"large batch shared experts T={T}")
+    res = X.moe_forward(x, torch.from_numpy(h).to(DEV), w1, w3, w2, 3, 1, 6, shared=sh)
+    torch.cuda.synchronize()
+    bits = [tuple(W.bf16_bits(m[s]) for m in sh) for s in range(2)]
+    ref = OracleOutputs(x, bf16_weights_of(w1, w3, w2), bits).y(res["ids"].cpu().numpy(),
+                                                               res["w"].cpu().numpy())
+    assert_ffn_close(OF.bf16_to_f64(W.bf16_bits(res["y"])), ref, f"shared T{T}")
+
+
+@pytest.mark.parametrize("fmt", ["fp8", "mxfp4"])
+def test_large_batch_group_share(fmt):
+    RUN[fmt](dict(N=32, k=4, d=288, f=224, T=260, logits="domains", Q=5), 3, 1, 4, "per_group",
+             groups=4, local=2, label=f"group share {fmt}")
