@@ -1527,7 +1527,9 @@ bool wide_batch(const FfnArgs& a) {
 template <int kW>
 void launch_gu_wide(const FfnArgs& a, hipStream_t stream) {
   const unsigned slots = a.max_active + a.shared_slots;
-  const long est = (a.est_active > 0 ? a.est_active : a.max_active) + a.shared_slots;
+  // slots, not experts: Mixtral T=1024 has 8 experts in about 20 slots
+  const int act = a.est_active > 0 ? slot_bound(a.est_active, a.T, a.k) : a.max_active;
+  const long est = std::min(act, a.max_active) + a.shared_slots;
   const unsigned b256 = (a.f + 127) / 128, b128 = (a.f + 63) / 64;
   if ((long)b256 * est * a.gu_splits >= (kW == kBf16 ? 1024 : 512))
     hipLaunchKernelGGL((gate_up_wide_kernel<kW, 256>), dim3(b256, slots, a.gu_splits), dim3(512), 0,

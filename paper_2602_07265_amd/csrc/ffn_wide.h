@@ -10,7 +10,7 @@
 // address work runs under the other's MFMAs; one wave a SIMD with twice the tile measured 930 us
 // against 720) take 64 of them and half of the token tiles each, or, up to 64 token rows, 32 of
 // them and all token tiles.
-//   A step is KB elements: its pieces are loaded into registers kSets steps before they are
+//   A step is KB elements: its pieces are loaded into registers two steps (kSets) before they are
 // written into one of two LDS buffers, one step before their MFMAs.
 //   A region is the MFMAs of 32 elements (of the hi or of the lo chunks in the down GEMM); the
 // operands of the next region are read during it.  One barrier a step, before its last region.
@@ -30,7 +30,6 @@ struct Wide {
   // elements per step; codes take twice as many where LDS has room, for the bytes in flight
   static constexpr int KB = kW != kBf16 && !kDown && NW == 256 ? 128 : 64;
   static constexpr int G = KB / 32 * AS;                 // regions per step
-  static constexpr int kSets = kDown && kW == kBf16 ? 1 : 2;
   static constexpr int XP = AS * KB / 8;                 // 16-byte pieces of an x row
   static constexpr int XR = kThreads / XP;               // x rows that the block's threads cover
   static constexpr int kXBytes = kSlotRows * XP * 16;    // of a buffer
@@ -71,6 +70,7 @@ __device__ __forceinline__ void wide_pass(const uint16_t* x, size_t ld, const in
   using W = Wide<kW, kDown, NW>;
   constexpr int KB = W::KB, AS = W::AS, G = W::G, NL = W::NL, kBuf = W::kBuf;
   constexpr int NX = (MW * NT * 16 + W::XR - 1) / W::XR;   // x pieces per thread and step
+  constexpr int kSets = 2;
   static_assert(NM * 16 * 2 * NW / 64 / MW == NW, "the waves hold the block's weight rows");
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
@@ -95,7 +95,7 @@ __device__ __forceinline__ void wide_pass(const uint16_t* x, size_t ld, const in
   const char* const ax = lds + (wave % MW * NT * 16 + n) * (W::XP * 16);
   const char* const bx = lds + W::kXBytes + (wave / MW * NM * 16 + n) * (W::WP * 16);
 
-  u32x4 v[W::kSets][NX], w[W::kSets][NL];
+  u32x4 v[kSets][NX], w[kSets][NL];
   const int steps = K / (2 * KB) * 2, last = (steps - 1) * KB;
   auto load = [&](int h, int k) {
     k = min(k, last);
@@ -153,13 +153,13 @@ __device__ __forceinline__ void wide_pass(const uint16_t* x, size_t ld, const in
   if (steps > 0) {
     bf16x8 xa[NT];
     BR b[2][NM];
-    uint8_t e[2][W::RB][NM];
+    uint8_t e[kSets][W::RB][NM];
 #pragma unroll
-    for (int h = 0; h < W::kSets; ++h) load(h, h * KB);
-    read_e(e[0], 0);
-    read_e(e[1], min(KB, last));
+    for (int h = 0; h < kSets; ++h) load(h, h * KB);
+#pragma unroll
+    for (int h = 0; h < kSets; ++h) read_e(e[h], min(h * KB, last));
     store(0, 0);
-    load(0, W::kSets * KB);
+    load(0, kSets * KB);
     __syncthreads();
     read_b(b[0], 0, 0);
 #pragma unroll
@@ -168,7 +168,6 @@ __device__ __forceinline__ void wide_pass(const uint16_t* x, size_t ld, const in
     // loaded with step k + (kSets + 1) KB
     auto step = [&](auto half, int k) {
       constexpr int h = decltype(half)::value;
-      constexpr int set = W::kSets == 2 ? h ^ 1 : 0;
 #pragma unroll
       for (int i = 0; i < G; ++i) {
         const int nb = i < G - 1 ? h : h ^ 1, ni = (i + 1) % G;       // the next region
@@ -177,8 +176,8 @@ __device__ __forceinline__ void wide_pass(const uint16_t* x, size_t ld, const in
         const int r = u / kPair, nr = nu / kPair;
         __builtin_amdgcn_sched_barrier(0);
         if (i == (G > 2 ? 1 : 0)) {
-          store(set, h ^ 1);
-          load(set, k + (W::kSets + 1) * KB);
+          store(h ^ 1, h ^ 1);
+          load(h ^ 1, k + (kSets + 1) * KB);
         }
         // b[parity of the read, counted over two steps]
         if (nr != r || i == G - 1)
