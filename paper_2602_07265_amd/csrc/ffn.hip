@@ -839,6 +839,107 @@ __launch_bounds__(kBlock) void gate_up_kernel(FfnArgs a) {
   XS_TIME(xs_times_gu, 2 * block_id3() + 1, 2u * kTimeBlocks);
 }
 
+// Gate/up of a few small experts that hold a few rows each, where the launch would otherwise
+// split d over blocks: here the four waves of a block split it over the same 16 columns and add
+// their sums through LDS, so there are no partial planes and no finish pass (4.7 us, most of it
+// its launch).  Each wave reads its own part of the token rows.  Measured, layer us (split grid
+// and finish pass -> this; steps of 2 / 4 / 8 groups): Qwen T=1 bf16 41.6 -> 37.0 / 38.0 / 41.0,
+// FP8 35.3 -> 32.9 / 32.0 / 32.8, MXFP4 36.8 -> 34.3 / 34.0 / 34.3; T=2 bf16 49.1 -> 45.0, FP8
+// 38.7 -> 36.5, MXFP4 35.7 -> 34.2.
+template <int U, int kW>
+__global__ __launch_bounds__(kBlock) void gate_up_narrow_kernel(FfnArgs a) {
+  using WT = WTile<kW, U>;
+  constexpr int KB = 32 * U;
+  SlotWork sw;
+  if (!slot_work(a, blockIdx.y, sw)) return;
+  XS_TIME(xs_times_gu, 2 * block_id3(), 2u * kTimeBlocks);
+  const int p0 = sw.p0, te = sw.te;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int n = lane & 15, g = lane >> 4;
+  const int d = a.d, f = a.f;
+  const int K = d / kWaves;                      // this wave's part (a multiple of 32)
+  const int kbase = wave * K;
+  const int col = blockIdx.x * kCols + n;
+  const size_t k0 = (size_t)kbase + (kW == kBf16 ? klane(g) : g * 8 * U);
+  typename WT::Ptr wp[2];
+  const size_t wrow = (size_t)col * d + k0;
+  if constexpr (kW == kBf16) {
+    wp[0].w = slot_w(a, sw, a.w1, a.sw1) + wrow;
+    wp[1].w = slot_w(a, sw, a.w3, a.sw3) + wrow;
+  } else if constexpr (kW == kFp8) {
+    wp[0].w = slot_q(a, sw, a.q1) + wrow;
+    wp[1].w = slot_q(a, sw, a.q3) + wrow;
+  } else {
+    const size_t r = (size_t)sw.e * f + col;
+    const int G = mx_granules(d);
+    const size_t emat = (size_t)sw.e * f * G * 8;
+    wp[0] = {a.q1 + r * (d / 2) + k0 / 2, mx_row(a.e1 + emat, col, G), (int)k0};
+    wp[1] = {a.q3 + r * (d / 2) + k0 / 2, mx_row(a.e3 + emat, col, G), (int)k0};
+  }
+  const float s1 = kW == kFp8 ? a.s1[(size_t)sw.e * f + col] : 1.0f;
+  const float s3 = kW == kFp8 ? a.s3[(size_t)sw.e * f + col] : 1.0f;
+  __shared__ floatx4 sums[kWaves][2][64];        // per 16-row tile: gate and up of every wave
+
+  for (int c0 = 0; c0 < te; c0 += 16) {
+    const int t = min(c0 + n, te - 1);
+    const int tok = sw.shared ? p0 - a.T * (a.k + sw.e) + t : a.perm[p0 + t] / a.k;
+    const uint16_t* const xr = a.x + (size_t)tok * d + kbase;
+    floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+    const int Kf = K / KB * KB, ut = (K - Kf) >> 5;
+    typename WT::Regs b[2];
+    bf16x8 x[U];
+    auto load = [&](typename WT::Regs (&rb)[2], bf16x8 (&rx)[U], int k) {
+#pragma unroll
+      for (int m = 0; m < 2; ++m) rb[m] = WT::load(wp[m], k);
+#pragma unroll
+      for (int u = 0; u < U; ++u) rx[u] = load8(xr + k + WT::koff(g, u));
+    };
+    if (Kf > 0) load(b, x, 0);
+    for (int k = 0; k < Kf; k += KB) {
+      typename WT::Regs nb[2];
+      bf16x8 nx[U];
+      load(nb, nx, min(k + KB, Kf - KB));        // past the last step: that step again
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) acc[m] = mfma(x[u], WT::operand(b[m], u), acc[m]);
+#pragma unroll
+      for (int m = 0; m < 2; ++m) b[m] = nb[m];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = nx[u];
+    }
+    if (ut) {                                    // the partial step
+      typename WT::Rest rb[2];
+#pragma unroll
+      for (int m = 0; m < 2; ++m) rb[m] = WT::load_rest(wp[m], Kf, g, ut);
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = load8(xr + Kf + 32 * min(u, ut - 1) + 8 * g);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (u >= ut) break;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) acc[m] = mfma(x[u], WT::operand_rest(rb[m], u), acc[m]);
+      }
+    }
+    sums[wave][0][lane] = acc[0];
+    sums[wave][1][lane] = acc[1];
+    __syncthreads();
+    // wave i finishes row 4g + i of each lane group: the waves' sums in order
+    float h1 = 0.f, h3 = 0.f;
+#pragma unroll
+    for (int v = 0; v < kWaves; ++v) {
+      h1 += sums[v][0][lane][wave];
+      h3 += sums[v][1][lane][wave];
+    }
+    h1 *= s1;
+    h3 *= s3;
+    if (c0 + 4 * g + wave < te)
+      store_hilo(a.h, p0 + c0 + 4 * g + wave, col, f, h1 / (1.0f + __expf(-h1)) * h3);
+    __syncthreads();                             // the next rows rewrite the sums
+  }
+  XS_TIME(xs_times_gu, 2 * block_id3() + 1, 2u * kTimeBlocks);
+}
+
 // NM: 16-row W2 tiles per wave (the launch picks it per weight format and batch shape).
 // Staged down instances are held to 2 waves per SIMD: left alone the compiler took 1 for the
 // 64-row bf16 and FP8 instances (FP8 DeepSeek T=32 down 166 -> 138 us with the hint).
@@ -1521,8 +1622,8 @@ bool wide_batch(const FfnArgs& a) {
 
 // Gate/up with 256 weight rows a block where that leaves at least 1024 blocks (bf16) or 512 (FP8
 // and MXFP4, whose steps are twice as long then), else 128 (two blocks a CU).  256 against 128
-// rows, layer us: bf16 Mixtral T=40 (560 blocks of 256) 427 / 390, DeepSeek T=64 M=24 (384) 476 / 461,
-// T=512 (1600) 2300 / 2317; FP8 DeepSeek T=64 M=32 (512) 331 / 348, a group share (128) 155 / 147;
+// rows, layer us: bf16 Mixtral T=40 (560 blocks of 256) 427 / 390, DeepSeek T=64 M=24 (384) 476 /
+// 461, T=512 (1600) 2300 / 2317; FP8 DeepSeek T=64 M=32 (512) 331 / 348, a group share (128) 155 / 147;
 // MXFP4 Qwen T=256 (384) 128 / 121, DeepSeek T=256 M=64 (1024) 571 / 642.
 template <int kW>
 void launch_gu_wide(const FfnArgs& a, hipStream_t stream) {
@@ -1547,9 +1648,29 @@ void launch_dn_wide(const FfnArgs& a, hipStream_t stream) {
                      stream, a);
 }
 
+// Gate/up with the waves of a block splitting d (gate_up_narrow_kernel): where the grid would
+// split d (few or small experts; its parts are multiples of 128, so d is one of 256) and no
+// expert can hold more than one tile of 16 rows, 4 on average (each block reads its rows of x for
+// 16 columns only).
+bool narrow_batch(const FfnArgs& a) {
+  return a.gu_splits > 1 && a.T <= 16 && a.est_active > 0 && a.d % (32 * kWaves) == 0 &&
+         (long)a.T * a.k <= 4L * a.est_active && a.n_shared == 0;
+}
+template <int U, int kW>
+void launch_gu_narrow(const FfnArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL((gate_up_narrow_kernel<U, kW>),
+                     dim3(a.f / kCols, a.max_active + a.shared_slots), dim3(kBlock), 0, stream, a);
+}
+
 }  // namespace
 
 hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
+  if (narrow_batch(a)) {
+    if (a.wfmt == kFp8) launch_gu_narrow<4, kFp8>(a, stream);
+    else if (a.wfmt == kMx4) launch_gu_narrow<4, kMx4>(a, stream);
+    else launch_gu_narrow<2, kBf16>(a, stream);
+    return hipGetLastError();
+  }
   const int cols = kWaves * kCols;            // one column tile per wave; launch_gu may take two
   const dim3 grid((a.f + cols - 1) / cols, a.max_active + a.shared_slots, a.gu_splits),
       block(kBlock);

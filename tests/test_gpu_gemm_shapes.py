@@ -36,6 +36,16 @@ def test_partial_steps_wide_launches(fmt):
     _case(fmt, 40, 120, 16, 1760, 160, 110, "wide down")
 
 
+# few small experts with a few rows each: the waves of a gate/up block split d (in 64 to 576
+# elements a wave, whole steps and partial ones)
+@FORMATS
+@pytest.mark.parametrize("T,N,k,d,f,M", [(1, 16, 4, 256, 96, 4), (6, 24, 2, 512, 32, 12),
+                                         (16, 40, 2, 1280, 160, 16), (2, 12, 8, 768, 224, 12),
+                                         (9, 20, 1, 2304, 64, 9)])
+def test_waves_split_d(fmt, T, N, k, d, f, M):
+    _case(fmt, T, N, k, d, f, M, "waves split d")
+
+
 # two experts hold every token: T rows each (past 128 in slots of nearly equal size), for each
 # count of token tiles; d and f around the large-batch launches' steps and pairs of steps
 @FORMATS
