@@ -1651,9 +1651,13 @@ void launch_dn_wide(const FfnArgs& a, hipStream_t stream) {
 // Gate/up with the waves of a block splitting d (gate_up_narrow_kernel): where the grid would
 // split d (few or small experts; its parts are multiples of 128, so d is one of 256) and no
 // expert can hold more than one tile of 16 rows, 4 on average (each block reads its rows of x for
-// 16 columns only).
+// 16 columns only).  FP8 takes it up to 1024 waves of 16 columns, where the grid no longer splits
+// but has one block a CU: DeepSeek T=1 (8 experts) 101 -> 88 us a layer; past that it gains and
+// loses with the shape (Mixtral T=1, 1792 waves, 84 -> 91, T=4, 4480 waves, 204 -> 179), bf16
+// loses there (DeepSeek T=1 141 -> 145), and MXFP4 does by 15-60 %.
 bool narrow_batch(const FfnArgs& a) {
-  return a.gu_splits > 1 && a.T <= 16 && a.est_active > 0 && a.d % (32 * kWaves) == 0 &&
+  const bool few = a.gu_splits > 1 || (a.wfmt == kFp8 && (long)a.est_active * (a.f / 16) <= 1024);
+  return few && a.T <= 16 && a.est_active > 0 && a.d % (32 * kWaves) == 0 &&
          (long)a.T * a.k <= 4L * a.est_active && a.n_shared == 0;
 }
 template <int U, int kW>
