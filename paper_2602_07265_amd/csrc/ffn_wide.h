@@ -20,9 +20,10 @@
 // lanes of a read into distinct banks (rows 16 bytes apart instead cost 4 conflict cycles a read).
 //   bf16: lane group g's elements of group u are 32u + 8g; FP8 and MXFP4: 16g + 8u of each 64, one
 // read for both groups.
-// Measured, us (staged pass -> this one): Mixtral T=1024 gate/up 2605 -> 720 (0.48 TFLOP, 667
-// TFLOP/s; the card clocks down to 1.9 GHz), down 1506 -> 570 (0.48 TFLOP with hi and lo); DeepSeek
-// T=512 M=96 gate/up 1980 -> 1120 (5.6 GB of weights, 5.0 TB/s), down 1149 -> 500 (5.6 TB/s).
+// Measured, us (staged pass -> this one): Mixtral T=1024 gate/up 2605 -> 700 (0.48 TFLOP, 687
+// TFLOP/s; a large library product reaches 1220 on this card, which clocks down to 1.9 GHz), down
+// 1506 -> 588 (0.48 TFLOP with hi and lo); DeepSeek T=512 M=96 gate/up 1983 -> 992 (5.6 GB of
+// weights, 5.7 TB/s), down 1149 -> 576 (2.8 GB, 4.9 TB/s).
 template <int kW, bool kDown, int NW>
 struct Wide {
   static constexpr int kThreads = 2 * NW;
