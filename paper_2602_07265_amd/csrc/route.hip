@@ -1,8 +1,8 @@
 // Expert selection for one MoE layer and one decode batch (XShare, arXiv 2602.07265):
 // router scoring, batch scores, greedy selection (flat Algorithm 2 or per-request +
 // batch Algorithms 3-4), refinement, and the token permutation consumed by the expert
-// GEMMs.  For decode-sized batches (T <= 64) one workgroup of 1024 threads does all of it:
-// the whole problem is a few thousand logits and is latency-, not throughput-bound, so the
+// GEMMs.  For decode-sized batches (one_group_tokens) one workgroup of 1024 threads does all of
+// it: the whole problem is a few thousand logits and is latency-, not throughput-bound, so the
 // kernel avoids LDS round trips in its inner loops: wave reductions use DPP, rankings compare
 // packed integer keys, and a token bitmask per expert turns every per-expert gather into
 // popcounts.  Larger batches run four kernels over the whole GPU (route_tokens_kernel and the
@@ -16,6 +16,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "internal.h"
 
@@ -422,34 +424,75 @@ __device__ int block_excl_scan(int v, int* s_wsum, int& total) {
 
 // Per-token list entry: bits 0-9 expert, bits 10-14 rank; kNoEntry = empty.
 
-// The one-workgroup selection (route_kernel) takes batches of up to 64 tokens: one token
-// bitmask per expert turns the per-expert gathers (scores, per-request scores, permutation)
-// into popcounts, and the keys of a wave's tokens stay in registers from the top-k to the
-// refinement.  It ends earlier where the four-kernel selection, about 20 us at any size here,
-// is faster (us a call, one workgroup -> four kernels): N=256 T=32 18.7 -> 20.4, T=48 22.4 ->
-// 20.8, T=64 27.6 -> 20.6, 16 requests of 4 31.4 -> 25.4; N=128 T=48 18.6 -> 20.0, T=64 21.4
-// -> 20.0; N=8 T=64 12.2 -> 19.9; or where a token's keys leave no registers for more.
-constexpr int kOccTokens = 64;
+// Tokens of the one-workgroup selection (route_kernel), at most; one_group_tokens says which
+// batches take it.  One token bitmask per expert turns the per-expert gathers (scores,
+// per-request scores, permutation) into popcounts, and the keys of a wave's tokens stay in
+// registers from the top-k to the refinement.  kFew: the instances for more tokens of at most
+// kFewRanks ranks each, whose rankings are short (no dense scores).
+constexpr int kFewRanks = 4;
+template <int Q, bool kFew>
+constexpr int max_tokens() {
+  if (kFew) return Q == 1 ? 128 : Q == 2 ? 112 : Q == 4 ? 72 : Q == 8 ? 52 : 32;
+  return Q <= 2 ? 64 : Q == 4 ? 40 : Q == 8 ? 24 : 16;
+}
+static_assert(max_tokens<1, true>() <= kSlotRows, "one slot holds all rows of an expert");
+
+// Batches of up to this many tokens take the one-workgroup selection: one launch, where the four
+// kernels need four and at least 15 us, but serial work that grows with T, k and N.  Measured, us
+// a call, one workgroup / four kernels, queued behind other GPU work and then in a stream of
+// selection calls alone (where four launches cost the host 24 us):
+//   N=64   k=1 T=128 16 / 16, 17 / 24   k=4 T=80 18 / 18, 17 / 24   T=112 22 / 18, 19 / 24
+//   N=128  k=1 T=112 17 / 16, 17 / 24   k=4 T=64 18 / 18, 17 / 24   T=80 21 / 19, 18 / 24
+//          k=6 T=64 20 / 20, 19 / 24    k=8 T=64 23 / 21, 21 / 24
+//   N=256  k=1 T=72 19 / 17, 17 / 24    k=2 T=56 18 / 18, 17 / 24   T=64 21 / 18, 19 / 24
+//          k=6 T=40 22 / 21, 20 / 24    16 requests of 4, k=2: 23 / 19, 21 / 25
+//   N=512  k=1 T=48 19 / 20, 18 / 24    k=4 T=33 23 / 22, 21 / 24   k=8 T=28 27 / 26, 25 / 24
+//   N=1024 k=1 T=32 24 / 23, 22 / 23    k=4 T=20 28 / 28, 25 / 25   k=8 T=16 27 / 27, 25 / 25
+// Picks per request add to the serial work like two more ranks.  Dense scores (a sum over all
+// experts in order) are slower in one workgroup from 40 tokens on.
 template <int Q>
-constexpr int small_tokens() { return Q == 1 ? 64 : Q == 2 ? 56 : Q == 4 ? 40 : Q == 8 ? 32 : 16; }
-constexpr int kSmallAssignments = kOccTokens * kMaxTopK;
-static_assert(small_tokens<1>() <= kOccTokens, "a bit per token");
+int one_group_tokens(const RouteArgs& a) {
+  const bool dense = a.score_mode == 1;
+  const int k = a.k + (a.req_offsets && a.m_r > 0 ? 2 : 0);
+  if (dense || k > kFewRanks) return Q == 2 && (dense || k > 6) ? 56 : max_tokens<Q, false>();
+  constexpr int kStep = Q == 1 ? 12 : Q == 2 ? 16 : Q == 4 ? 12 : Q == 8 ? 8 : 4;
+  return std::max(max_tokens<Q, true>() - kStep * (k - 1), max_tokens<Q, false>());
+}
 
 __device__ __forceinline__ uint64_t below(int i) { return i >= 64 ? ~0ull : ((1ull << i) - 1ull); }
 
+// A set of tokens, kW words.
+template <int kW>
+struct TokenMask {
+  uint64_t w[kW];
+  __device__ void add(int i) {
+    atomicOr(reinterpret_cast<unsigned long long*>(&w[kW > 1 ? i >> 6 : 0]), 1ull << (i & 63));
+  }
+  __device__ int count() const {
+    int c = __popcll(w[0]);
+    if constexpr (kW > 1) c += __popcll(w[1]);
+    return c;
+  }
+  __device__ int count_below(int i) const {       // 0 <= i <= 64 kW
+    int c = __popcll(w[0] & below(i));
+    if constexpr (kW > 1) c += __popcll(w[1] & below(max(i - 64, 0)));
+    return c;
+  }
+};
+
 // Groups the entries by expert (ascending), tokens ascending inside: s_off[e] is the start
-// of expert e's run in s_list, which holds entry indices p = i * k + r.  Needs T <= 64 and
-// s_occ zeroed; every thread must call.  Returns this thread's expert count (j = tid < N).
-__device__ int group_by_expert(const uint16_t* s_ent, uint64_t* s_occ, int* s_off,
+// of expert e's run in s_list, which holds entry indices p = i * k + r.  Needs s_occ zeroed;
+// every thread must call.  Returns this thread's expert count (j = tid < N).
+template <int kW>
+__device__ int group_by_expert(const uint16_t* s_ent, TokenMask<kW>* s_occ, int* s_off,
                                uint16_t* s_list, int* s_wsum, int TK, int k, int N, int& total) {
   const int tid = threadIdx.x;
   for (int p = tid; p < TK; p += kThreads) {
     const uint32_t ent = s_ent[p];
-    if (ent != kNoEntry) atomicOr(reinterpret_cast<unsigned long long*>(&s_occ[ent & 1023u]),
-                                  1ull << (p / k));
+    if (ent != kNoEntry) s_occ[ent & 1023u].add(p / k);
   }
   __syncthreads();
-  const int cnt = tid < N ? __popcll(s_occ[tid]) : 0;
+  const int cnt = tid < N ? s_occ[tid].count() : 0;
   const int off = block_excl_scan(cnt, s_wsum, total);
   if (tid < N) s_off[tid] = off;
   if (tid == N - 1) s_off[N] = off + cnt;
@@ -458,7 +501,7 @@ __device__ int group_by_expert(const uint16_t* s_ent, uint64_t* s_occ, int* s_of
     const uint32_t ent = s_ent[p];
     if (ent == kNoEntry) continue;
     const int e = (int)(ent & 1023u);
-    s_list[s_off[e] + __popcll(s_occ[e] & below(p / k))] = (uint16_t)p;
+    s_list[s_off[e] + s_occ[e].count_below(p / k)] = (uint16_t)p;
   }
   __syncthreads();
   return cnt;
@@ -648,13 +691,16 @@ __device__ __forceinline__ bool select_set(const RouteArgs& a, GreedyTables& sh,
   return sel;
 }
 
-template <int Q>
+template <int Q, bool kFew>
 __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
-  __shared__ __align__(16) uint16_t s_ent[kSmallAssignments];  // (token, rank) -> expert | rank
-  __shared__ float s_g[kSmallAssignments];                     // vanilla gate of that entry
-  __shared__ float s_vh[kSmallAssignments];                    // vanilla logit of that entry
-  __shared__ uint16_t s_list[kSmallAssignments];               // entries grouped by expert
-  __shared__ __align__(16) uint64_t s_occ[kMaxExperts];        // token bitmask per expert
+  constexpr int kTokens = max_tokens<Q, kFew>();
+  constexpr int kEntries = kTokens * (kFew ? kFewRanks : kMaxTopK);
+  constexpr int kW = (kTokens + 63) / 64;
+  __shared__ __align__(16) uint16_t s_ent[kEntries];           // (token, rank) -> expert | rank
+  __shared__ float s_g[kEntries];                              // vanilla gate of that entry
+  __shared__ float s_vh[kEntries];                             // vanilla logit of that entry
+  __shared__ uint16_t s_list[kEntries];                        // entries grouped by expert
+  __shared__ __align__(16) TokenMask<kW> s_occ[kMaxExperts];   // tokens of each expert
   __shared__ GreedyTables sh;
   __shared__ int s_off[kMaxExperts + 1];
   __shared__ uint8_t s_tier1[kMaxExperts];                   // picked by some request
@@ -671,9 +717,6 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   const bool ep = a.G > 0;
   const int TK = T * k;
 
-  // tokens per wave whose keys stay in registers (1024 threads allow 128 VGPRs each); the
-  // launch takes this kernel for batches of up to that many
-  constexpr int kCache = (small_tokens<Q>() + kWaves - 1) / kWaves;
   // Two tokens per wave (one per half) where a token's experts fit 8 per lane and the batch
   // gives a wave more than one token, except with dense scores (their softmax sums every
   // expert of the token in index order): token pairs p = wave, wave + 16, ..., pair p
@@ -681,22 +724,25 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   // DeepSeek T=32 25.8 -> 25.0, Qwen T=64 34.4 -> 30.7, speculative T=64 40.0 -> 37.5; with
   // at most one token per wave (T <= 16) the half-wave rounds only add: T=8 18.0 -> 19.5.
   // Four tokens per wave (one per 16-lane row) where a token's experts fit 8 per lane, its
-  // ranks fit in a row and the batch gives a wave more than two tokens, with every quad's
-  // remaining keys kept in registers (token quads p = wave, wave + 16, ...).
+  // ranks fit in a row and the batch gives a wave more than two tokens (token quads p = wave,
+  // wave + 16, ...).  The keys left after the top-k stay in registers (1024 threads allow 128
+  // each): tokens, pairs and quads per wave.
   constexpr bool kHalves = Q <= 4;
   constexpr int Q2 = 2 * Q;
-  constexpr int kCacheP = Q2 <= 4 ? 4 : (Q2 <= 8 ? 2 : 1);   // pairs per wave in registers
   constexpr bool kQuads = Q <= 2;
   constexpr int Q4 = 4 * Q;
-  constexpr int kCacheQ = Q4 <= 4 ? 4 : 2;                    // quads per wave in registers
+  // (kFew: only more than 16 tokens, so in pairs or quads where these are)
+  static_assert(max_tokens<Q, false>() >= kWaves, "kFew: pairs or quads");
+  constexpr int kCache = kFew && kHalves ? 0 : (kTokens + kWaves - 1) / kWaves;
+  constexpr int kCacheP = (kTokens + 2 * kWaves - 1) / (2 * kWaves);
+  constexpr int kCacheQ = (kTokens + 4 * kWaves - 1) / (4 * kWaves);
   const int n_quads = (T + 3) >> 2;
-  const bool quads = kQuads && !dense && k <= 16 && T > 2 * kWaves &&
-                     n_quads <= kCacheQ * kWaves;
+  const bool quads = kQuads && !dense && k <= 16 && T > 2 * kWaves;
   const bool halves = kHalves && !dense && T > kWaves && !quads;
   const int hh = lane >> 5, sl = lane & 31;
   const int qr = lane >> 4, ql = lane & 15;
   const int n_pairs = (T + 1) >> 1;
-  uint32_t kc[kCache][Q];
+  uint32_t kc[kCache > 0 ? kCache : 1][Q];
   uint32_t kcp[kHalves ? kCacheP : 1][kHalves ? Q2 : 1];
   uint32_t kcq[kQuads ? kCacheQ : 1][kQuads ? Q4 : 1];
   float raw_next[Q];
@@ -716,7 +762,7 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   if (tid < 8) sh.cnt[tid] = 0;
   for (int j = tid; j < kMaxExperts; j += kThreads) {
     s_tier1[j] = 0;
-    s_occ[j] = 0;
+    s_occ[j] = TokenMask<kW>{};
     sh.gload[j] = 0;
     sh.gcand[j] = 0;
     sh.hist[j] = 0;
@@ -765,9 +811,8 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   }
 
   // ---- (a) per token: plain top-k and its gates (Section 2.2); dense softmax if requested.
-  //      The next token's row is loaded while the current one is ranked; for batches of
-  //      up to four tokens per wave the keys left after the top-k (all experts but the
-  //      token's top-k) stay in registers for the refinement.
+  //      The next token's row is loaded while the current one is ranked; the keys left after
+  //      the top-k (all experts but the token's top-k) stay in registers for the refinement.
   // Token i: its plain top-k, gates and entries; `left` receives the keys that remain
   // after the top-k.  The wave's next row is loaded meanwhile.
   auto plain_topk = [&](int i, uint32_t (&left)[Q]) {
@@ -910,14 +955,13 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
       unsigned inUr = 0, inS0r = 0;
 #pragma unroll
       for (int q = 0; q < Q; ++q) sr[q] = 0.0f;
-      const uint64_t range = below(hi) & ~below(lo);
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         const int jq = lane + 64 * q;
         if (jq >= N) continue;
-        const uint64_t m = s_occ[jq];
-        const int n = __popcll(m & range);
-        const int o = s_off[jq] + __popcll(m & below(lo));
+        const int before = s_occ[jq].count_below(lo);
+        const int n = s_occ[jq].count_below(hi) - before;
+        const int o = s_off[jq] + before;
         for (int t0 = 0; t0 < n; t0 += 8) {   // loads ahead of the ordered adds, as in (b)
           float gq[8];
           uint32_t eq[8];
@@ -1097,7 +1141,7 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
 
   // ---- (f) permutation: rows grouped by expert (ascending), tokens ascending inside
   int total = 0, off = 0;
-  for (int jj = tid; jj < kMaxExperts; jj += kThreads) s_occ[jj] = 0;
+  for (int jj = tid; jj < kMaxExperts; jj += kThreads) s_occ[jj] = TokenMask<kW>{};
   __syncthreads();
   const int cnt =
       group_by_expert(s_ent, s_occ, s_off, s_list, sh.wsum, TK, k, N, total);
@@ -1112,7 +1156,6 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
   // The active list puts experts with more than kHeavyRows routed rows first (in expert
   // order), then the others: their GEMM blocks run longest, so they start first instead of
   // trailing the launch.  One scan counts both classes (16 bits each).
-  static_assert(kOccTokens <= kSlotRows, "one slot holds all rows of an expert");
   const bool heavy = listed && cnt > kHeavyRows;
   int packed_total = 0;
   const int packed = block_excl_scan(listed ? (heavy ? 1 : (1 << 16)) : 0, sh.wsum, packed_total);
@@ -1521,8 +1564,11 @@ __global__ __launch_bounds__(kThreads) void route_lists_kernel(RouteArgs a) {
 
 template <int Q>
 hipError_t launch_route_q(const RouteArgs& a, hipStream_t stream) {
-  if (a.T <= small_tokens<Q>()) {
-    hipLaunchKernelGGL(route_kernel<Q>, dim3(1), dim3(kThreads), 0, stream, a);
+  if (a.T <= one_group_tokens<Q>(a)) {
+    if (a.T <= max_tokens<Q, false>())
+      hipLaunchKernelGGL((route_kernel<Q, false>), dim3(1), dim3(kThreads), 0, stream, a);
+    else
+      hipLaunchKernelGGL((route_kernel<Q, true>), dim3(1), dim3(kThreads), 0, stream, a);
     return hipGetLastError();
   }
   const int units = a.N + (a.req_offsets && a.m_r > 0 ? a.R : 0);

@@ -35,6 +35,25 @@ def test_large_batches_equal_the_oracle(T, N, k):
         assert_route_equal(got, oracle_route(h, k, *args, **more), label)
 
 
+# the instances for few ranks (token sets of two words past 64) and the first batches past them
+@pytest.mark.parametrize("T,N,k", [
+    (65, 8, 1), (128, 64, 1), (129, 64, 1), (116, 20, 2), (117, 20, 2), (92, 64, 4), (93, 33, 4),
+    (65, 65, 2), (112, 128, 1), (113, 128, 1), (80, 100, 3), (81, 100, 3), (41, 129, 4),
+    (72, 256, 1), (73, 256, 1), (60, 200, 2), (41, 256, 3), (25, 257, 4), (52, 512, 1),
+    (53, 512, 1), (17, 513, 1), (32, 1024, 1), (33, 1024, 1), (20, 1000, 4), (21, 1000, 4)])
+def test_few_ranks_equal_the_oracle(T, N, k):
+    test_large_batches_equal_the_oracle(T, N, k)
+
+
+@pytest.mark.parametrize("T,N,k", [(65, 64, 1), (100, 128, 1), (72, 256, 1), (40, 300, 2)])
+def test_few_ranks_refuse_bad_offsets(T, N, k):
+    h = np.random.default_rng(3).standard_normal((T, N)).astype(np.float32)
+    for off in ([0, 5, 5, T], [1, T], [0, 9, T + 1], [0, T - 1]):
+        got = gpu_route(h, k, 1, 8, offsets=off, m_r=1, device_offsets_only=True)
+        assert got["stats"][0] == -1 and not got["sel_mask"].any()
+        assert (got["ids"] == -1).all() and not got["w"].any()
+
+
 @pytest.mark.parametrize("T", [65, 500])
 def test_large_batches_refuse_bad_offsets_and_groups(T):
     """Offsets and group maps seen only on the device: nothing is selected."""
