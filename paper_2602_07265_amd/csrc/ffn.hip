@@ -1535,38 +1535,48 @@ template <int U, int kW, int CT, bool kRest>
 void launch_gu(const FfnArgs& a, dim3 grid, hipStream_t stream) {
   const dim3 block(kBlock);
   grid.x = (a.f + CT * kWaves * kCols - 1) / (CT * kWaves * kCols);
-  if (grid.z > 1) {
-    hipLaunchKernelGGL((gate_up_kernel<U, true, kW, CT, kRest>), grid, block, 0, stream, a);
-    return;
-  }
-  int s_main = (int)grid.y, ts = 1;
-  if constexpr (!kRest) {
+  if constexpr (kRest) {
+    hipLaunchKernelGGL((gate_up_kernel<U, false, kW, CT, true>), grid, block, 0, stream, a);
+  } else if (grid.z > 1) {
+    hipLaunchKernelGGL((gate_up_kernel<U, true, kW, CT, false>), grid, block, 0, stream, a);
+  } else {
     static std::atomic<int> resident{0};
-    ts = gu_tail_split<U>(
+    int s_main = (int)grid.y;
+    const int ts = gu_tail_split<U>(
         a, grid, resident_blocks(gate_up_kernel<U, false, kW, CT, false>, resident), s_main);
-  }
-  if (s_main > 0)
-    hipLaunchKernelGGL((gate_up_kernel<U, false, kW, CT, kRest>), dim3(grid.x, s_main, 1), block, 0,
-                       stream, a);
-  if constexpr (!kRest)
+    if (s_main > 0)
+      hipLaunchKernelGGL((gate_up_kernel<U, false, kW, CT, false>), dim3(grid.x, s_main, 1), block,
+                         0, stream, a);
     if (ts > 1) launch_gu_tail<U, kW, CT>(a, grid, s_main, ts, stream);
+  }
 }
 
-// Step of the launches over reductions that are no multiple of the format's own: half of it for
-// MXFP4 (its 8-word partial step spilled 80 registers), else the same.
+// Steps for reductions that are no multiple of the full step, U groups of 32: half of it where it
+// is whole (always in the parts of a split reduction, multiples of 128) and the partial-step
+// instance would be slower.  MXFP4 at odd multiples of 128, layer us, partial-step instance ->
+// whole half steps: d=4224 f=2944 T=4 139 -> 125, T=32 287 -> 256, d=5120 f=1664 195 -> 177.
+constexpr int half_step(int U) { return U == 8 ? 4 : U; }
+// Step of the partial-step instances: half for MXFP4 (its 8-word one spilled 80 registers).
 template <int kW, int U>
-constexpr int rest_step() { return kW == kMx4 && U == 8 ? 4 : U; }
+constexpr int rest_step() { return kW == kMx4 ? half_step(U) : U; }
+
+template <int kW, int U, int CT>
+void launch_gu_step(const FfnArgs& a, int K, dim3 grid, hipStream_t stream) {
+  constexpr int H = half_step(U);
+  if (K % (32 * U) == 0)
+    launch_gu<U, kW, CT, false>(a, grid, stream);
+  else if (grid.z > 1 || (kW == kMx4 && K % (32 * H) == 0))
+    launch_gu<H, kW, CT, false>(a, grid, stream);
+  else
+    launch_gu<rest_step<kW, U>(), kW, CT, true>(a, grid, stream);
+}
 
 // U2 / U1: steps of two-tile and of one-tile launches for weight format kW, over reductions of K.
 template <int kW, int U2, int U1>
 void launch_gu_fmt(const FfnArgs& a, int K, dim3 grid, hipStream_t stream) {
-  if (gu_two_tiles(a, kW, grid.z)) {
-    if (K % (32 * U2) == 0) launch_gu<U2, kW, 2, false>(a, grid, stream);
-    else launch_gu<rest_step<kW, U2>(), kW, 2, true>(a, grid, stream);
-  } else {
-    if (K % (32 * U1) == 0) launch_gu<U1, kW, 1, false>(a, grid, stream);
-    else launch_gu<rest_step<kW, U1>(), kW, 1, true>(a, grid, stream);
-  }
+  static_assert(half_step(U2) <= 4 && half_step(U1) <= 4, "whole in the parts of a split");
+  if (gu_two_tiles(a, kW, grid.z)) launch_gu_step<kW, U2, 2>(a, K, grid, stream);
+  else launch_gu_step<kW, U1, 1>(a, K, grid, stream);
 }
 
 // Blocks of a down instance that the GPU runs at once.
@@ -1581,8 +1591,12 @@ void launch_down_fmt(const FfnArgs& a, hipStream_t stream) {
   const int cols = kWaves * kCols * NM;
   const int slots = a.max_active + a.shared_slots;
   const dim3 grid((a.d + cols - 1) / cols, slots, a.splits), block(kBlock);
-  if ((a.f / a.splits) % (32 * U) == 0)
+  constexpr int H = half_step(U);
+  const int K = a.f / a.splits;
+  if (K % (32 * U) == 0)
     hipLaunchKernelGGL((down_kernel<U, kW, NM, false, TL>), grid, block, 0, stream, a);
+  else if (K % (32 * H) == 0)
+    hipLaunchKernelGGL((down_kernel<H, kW, NM, false, TL>), grid, block, 0, stream, a);
   else
     hipLaunchKernelGGL((down_kernel<rest_step<kW, U>(), kW, NM, true, TL>), grid, block, 0, stream,
                        a);

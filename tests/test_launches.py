@@ -48,3 +48,42 @@ def test_every_batch_size_has_an_instance_for_its_tokens(score, reqs):
         few = m[2] == "true"
         assert c["T"] <= limit[int(m[1])][few], (c, names)
         assert not few or (c["k"] <= 4 and score != "dense" and c["T"] > limit[int(m[1])][0]), c
+
+
+def layer(T, N, k, M, d, f, fmt="bf16", **more):
+    return dict(T=T, N=N, k=k, M=M, d=d, f=f, fmt=fmt, **more)
+
+
+def _instance(names, kernel):
+    """Template arguments of the one launch of `kernel`."""
+    found = [re.fullmatch(kernel + r"<(.*)>", n) for n in names]
+    found = [m for m in found if m]
+    assert len(found) == 1, (kernel, names)
+    return found[0][1].split(", ")
+
+
+@pytest.mark.parametrize("T,N,M,d,f", [(4, 96, 20, 4224, 2944), (32, 96, 48, 4224, 2944),
+                                       (32, 64, 48, 2688, 1408), (32, 96, 48, 5120, 1664)])
+def test_mxfp4_whole_half_steps(T, N, M, d, f):
+    """Reductions of odd multiples of 128 with MXFP4 weights run whole 128-element steps: the
+    partial-step instances are 10 to 12 % slower there."""
+    (names,) = _names([layer(T, N, 6, M, d, f, "mxfp4")])
+    for kernel, args, K in (("gate_up_kernel", slice(0, 5, 4), d), ("down_kernel", slice(0, 4, 3), f)):
+        step, rest = _instance(names, kernel)[args]
+        assert rest == "false" and K % (32 * int(step)) == 0, (kernel, names)
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp8", "mxfp4"])
+def test_split_reductions_run_whole_steps(fmt):
+    """The parts of a split reduction are multiples of 128."""
+    cases = [layer(T, 16, 2, M, d, f, fmt) for T in (20, 32) for M in (3, 6, 8)
+             for d in (512, 768, 1024, 1536, 2304, 2816) for f in (256, 768, 1408)]
+    seen = 0
+    for c, one in zip(cases, launches(cases)):
+        for name, grid, _ in one:
+            m = re.fullmatch(r"gate_up_kernel<(\d+), (\w+), \d+, \d+, (\w+)>", name)
+            if m and grid[2] > 1:
+                seen += 1
+                assert m[2] == "true" and m[3] == "false", (c, name)
+                assert (c["d"] // grid[2]) % (32 * int(m[1])) == 0, (c, name, grid)
+    assert seen > 10
