@@ -302,8 +302,9 @@ struct Stage {
 // for step s and the B operand of MFMA u.  `koff(g, u)`: the reduction offset, within a
 // step, of lane group g's elements in MFMA u (the A operand reads the same).
 // The `rest` members serve the last, partial step of a reduction that is no multiple of the
-// step: `ut` MFMAs of 32 elements (1 <= ut < U), elements 32u + 8g of each lane group, so that
-// every lane of an MFMA has elements and nothing past the row is read.
+// step: elements 32u + 8g of each lane group in MFMA u, so that every lane of an MFMA has
+// elements.  load_rest takes the MFMAs u0 <= u < n, each from a constant offset (clamped addresses
+// took registers for every one of them).
 template <int kW, int U>
 struct WTile;
 template <int U>
@@ -319,10 +320,11 @@ struct WTile<kBf16, U> {
     return r;
   }
   __device__ static bf16x8 operand(const Regs& r, int u) { return r.w[u]; }
-  __device__ static Rest load_rest(const Ptr& p, int s, int, int ut) {
+  __device__ static Rest load_rest(const Ptr& p, int s, int, int u0, int n) {
     Rest r;
 #pragma unroll
-    for (int u = 0; u < U; ++u) r.w[u] = load8(p.w + s + 32 * min(u, ut - 1));
+    for (int u = 0; u < U; ++u)
+      if (u >= u0 && u < n) r.w[u] = load8(p.w + s + 32 * u);
     return r;
   }
   __device__ static bf16x8 operand_rest(const Rest& r, int u) { return r.w[u]; }
@@ -340,11 +342,12 @@ struct WTile<kFp8, U> {
     return r;
   }
   __device__ static bf16x8 operand(const Regs& r, int u) { return fp8x8_to_bf16(r.w[u]); }
-  __device__ static Rest load_rest(const Ptr& p, int s, int g, int ut) {
+  __device__ static Rest load_rest(const Ptr& p, int s, int g, int u0, int n) {
     const uint8_t* const w = p.w - (8 * U - 8) * g + s;
     Rest r;
 #pragma unroll
-    for (int u = 0; u < U; ++u) r.w[u] = load_q8(w + 32 * min(u, ut - 1));
+    for (int u = 0; u < U; ++u)
+      if (u >= u0 && u < n) r.w[u] = load_q8(w + 32 * u);
     return r;
   }
   __device__ static bf16x8 operand_rest(const Rest& r, int u) { return operand(r, u); }
@@ -370,14 +373,15 @@ struct WTile<kMx4, U> {
     const uint32_t e = r.e;
     return fp4x8_to_bf16(r.q.w[u], e8m0_scale((e >> (8 * (u >> 2))) & 0xFFu));
   }
-  __device__ static Rest load_rest(const Ptr& p, int s, int g, int ut) {
+  __device__ static Rest load_rest(const Ptr& p, int s, int g, int u0, int n) {
     const uint8_t* const w = p.w - (4 * U - 4) * g + s / 2;
     const int k = p.k - 8 * U * g + s;
     Rest r;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      r.w[u] = *reinterpret_cast<const uint32_t*>(w + 16 * min(u, ut - 1));
-      r.e[u] = (uint8_t)load_mx_scales<1>(p.sc, k + 32 * min(u, ut - 1));
+      if (u < u0 || u >= n) continue;
+      r.w[u] = *reinterpret_cast<const uint32_t*>(w + 16 * u);
+      r.e[u] = (uint8_t)load_mx_scales<1>(p.sc, k + 32 * u);
     }
     return r;
   }
@@ -389,7 +393,7 @@ struct WTile<kMx4, U> {
 // NT: token tiles of the pass (R <= TR * NT rows); NL: loads per thread and step, at least
 // ceil(R * P / 256) (pieces beyond R * P repeat the last one).  Staged row r (r < R) is
 // x[tok[r] * ld ...], x already offset to this block's reduction range.  acc[m][rt]: the sums of
-// weight tile m and token tile rt.  kRest: K may be no multiple of the step (k_first is 0).
+// weight tile m and token tile rt.  kRest: K is no multiple of the step (k_first is 0).
 template <int kW, int U, bool kDown, int NM, int NT, int NL, bool kRest, int TA>
 __device__ __forceinline__ void block_pass(const uint16_t* x, size_t ld, const int* tok, int R,
                                            const typename WTile<kW, U>::Ptr (&wp)[NM], int K,
@@ -418,24 +422,17 @@ __device__ __forceinline__ void block_pass(const uint16_t* x, size_t ld, const i
 
   u32x4 v[NL];
   typename WT::Regs b[NM];
-  // the partial step's loads (from k = Kf on; a piece past the row reads the row's start, and
-  // no MFMA takes it) and its MFMAs
-  const int Kf = kRest ? K / KB * KB : K, ut = (K - Kf) >> 5;
+  // kRest: the reduction ends in a partial step of `ut` MFMAs of 32 elements, the last ut of the
+  // full step that ends with it (its loads then run under the step before it, as every step's
+  // do), or the first ut of one that starts with it where it is shorter than a step.  The 64-row
+  // down instances leave the short case to the 32-row ones: with it they spilled.
+  constexpr bool kShort = !(kDown && NM > 2);
+  const int ut = K % KB >> 5, Kf = K - 32 * ut;
   typename WT::Rest rb[kRest ? NM : 1];
-  auto load_rest = [&]() {
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int q = min(t + i * kBlock, R * S::P - 1);
-      v[i] = *reinterpret_cast<const u32x4*>(
-          src[i] + (q % S::P < 4 * S::AS * ut ? S::AS * Kf : -(q % S::P) * 8));
-    }
-#pragma unroll
-    for (int m = 0; m < NM; ++m) rb[kRest ? m : 0] = WT::load_rest(wp[m], Kf, g, ut);
-  };
-  auto step_rest = [&](const uint16_t* cur) {
+  auto step_rest = [&](const uint16_t* cur, int u0, int u1) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (u >= ut) break;
+      if (u < u0 || u >= u1) continue;
       const int ka = S::AS * (32 * u + 8 * g);
       bf16x8 xa[NT];
 #pragma unroll
@@ -449,12 +446,19 @@ __device__ __forceinline__ void block_pass(const uint16_t* x, size_t ld, const i
       }
     }
   };
-  if (kRest && Kf == 0) {                  // a reduction shorter than one step
-    load_rest();
+  if (kRest && kShort && Kf == 0) {
+    // a piece past the row reads the row's start; no MFMA takes it
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int piece = min(t + i * kBlock, R * S::P - 1) % S::P;
+      v[i] = *reinterpret_cast<const u32x4*>(src[i] - (piece < 4 * S::AS * ut ? 0 : piece * 8));
+    }
+#pragma unroll
+    for (int m = 0; m < NM; ++m) rb[kRest ? m : 0] = WT::load_rest(wp[m], 0, g, 0, ut);
 #pragma unroll
     for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(lds + wofs[i]) = v[i];
     __syncthreads();
-    step_rest(lds);
+    step_rest(lds, 0, ut);
     __syncthreads();
     return;
   }
@@ -502,21 +506,27 @@ __device__ __forceinline__ void block_pass(const uint16_t* x, size_t ld, const i
   };
   // the pass starts at step k_first and wraps around (two plain loops: a wrap test inside
   // one loop measured slower)
-  for (int kn = k_first + KB; kn < Kf; kn += KB) advance(kn);
+  for (int kn = k_first + KB; kn < (kRest ? Kf : K); kn += KB) advance(kn);
   for (int kn = 0; kn < k_first; kn += KB) advance(kn);
   if constexpr (kRest) {
-    // not overlapped with the last full step: holding both steps' weights spilled registers
-    // or cost a wave per SIMD
-    step(lds + buf * kStageRows * S::LS);
-    if (ut) {
-      __builtin_amdgcn_sched_barrier(0);
-      load_rest();
-      uint16_t* const nxt = lds + (buf ^ 1) * kStageRows * S::LS;
+    const int kr = K - KB;
 #pragma unroll
-      for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(nxt + wofs[i]) = v[i];
-      __syncthreads();
-      step_rest(nxt);
+    for (int i = 0; i < NL; ++i) v[i] = *reinterpret_cast<const u32x4*>(src[i] + S::AS * kr);
+    // bf16: the first half of that step is loaded only where the partial step reaches into it (a
+    // gate/up of d an odd multiple of 128 1 % faster; FP8 and MXFP4 measured no gain)
+    if (kW != kBf16 || ut > U / 2) {
+#pragma unroll
+      for (int m = 0; m < NM; ++m) rb[m] = WT::load_rest(wp[m], kr, g, 0, U);
+    } else {
+#pragma unroll
+      for (int m = 0; m < NM; ++m) rb[m] = WT::load_rest(wp[m], kr, g, U / 2, U);
     }
+    step(lds + buf * kStageRows * S::LS);
+    uint16_t* const nxt = lds + (buf ^ 1) * kStageRows * S::LS;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(nxt + wofs[i]) = v[i];
+    __syncthreads();
+    step_rest(nxt, U - ut, U);
   } else {
     step(lds + buf * kStageRows * S::LS);
   }
@@ -740,8 +750,15 @@ __device__ __forceinline__ const uint8_t* slot_q(const FfnArgs& a, const SlotWor
 // blocks (the launch takes two only for grids that stay large).
 // The MXFP4 one-tile instance is held to 168 registers (3 waves per SIMD): left alone the
 // compiler took 175 and 2 waves, and DeepSeek T=8 gate/up ran 14 % slower.  So are the FP8
-// instances of up to 4 words a step (XS_Q8_GU_W3), but not the two-tile one with a partial
-// step, which would spill.  The other instances with a partial step are held to 2.
+// instances of up to 4 words a step (XS_Q8_GU_W3).  The two-tile bf16 and FP8 instances with a
+// partial step are compiled for at most 1 and 2 waves, and then need the registers that keep
+// them there: with one wave more they ran slower (rows that start inside a cache line share it
+// with the next row; gate/up us at d=4128 f=2976 T=16 M=40: bf16 384 -> 408, FP8 236 -> 247).
+template <int kW, int U, int CT, bool kRest>
+constexpr int gu_max_waves() {
+  if (kRest && CT == 2 && kW != kMx4) return kW == kBf16 ? 1 : 2;
+  return 8;
+}
 template <int kW, int U, int CT, bool kRest>
 constexpr int gu_waves() {
   if (kW == kMx4 && CT == 1) return 3;
@@ -749,7 +766,8 @@ constexpr int gu_waves() {
   return kRest && !(kW == kBf16 && CT == 2) ? 2 : 1;
 }
 template <int U, bool kSplit, int kW, int CT, bool kRest>
-__global__ __attribute__((amdgpu_waves_per_eu(gu_waves<kW, U, CT, kRest>())))
+__global__ __attribute__((amdgpu_waves_per_eu(gu_waves<kW, U, CT, kRest>(),
+                                              gu_max_waves<kW, U, CT, kRest>())))
 __launch_bounds__(kBlock) void gate_up_kernel(FfnArgs a) {
   constexpr int NM = 2 * CT;                   // weight tiles: W1 and W3 of each column tile
   SlotWork sw;
@@ -911,7 +929,7 @@ __global__ __launch_bounds__(kBlock) void gate_up_narrow_kernel(FfnArgs a) {
     if (ut) {                                    // the partial step
       typename WT::Rest rb[2];
 #pragma unroll
-      for (int m = 0; m < 2; ++m) rb[m] = WT::load_rest(wp[m], Kf, g, ut);
+      for (int m = 0; m < 2; ++m) rb[m] = WT::load_rest(wp[m], Kf, g, 0, ut);
 #pragma unroll
       for (int u = 0; u < U; ++u) x[u] = load8(xr + Kf + 32 * min(u, ut - 1) + 8 * g);
 #pragma unroll
@@ -1586,20 +1604,23 @@ int down_resident() {
   return resident_blocks(down_kernel<U, kW, NM, kRest, TL>, cached);
 }
 
-template <int U, int kW, int NM, int TL = XS_DOWN_TL>
-void launch_down_fmt(const FfnArgs& a, hipStream_t stream) {
+template <int U, int kW, int NM, bool kRest, int TL>
+void launch_down_step(const FfnArgs& a, hipStream_t stream) {
   const int cols = kWaves * kCols * NM;
-  const int slots = a.max_active + a.shared_slots;
-  const dim3 grid((a.d + cols - 1) / cols, slots, a.splits), block(kBlock);
-  constexpr int H = half_step(U);
+  hipLaunchKernelGGL((down_kernel<U, kW, NM, kRest, TL>),
+                     dim3((a.d + cols - 1) / cols, a.max_active + a.shared_slots, a.splits),
+                     dim3(kBlock), 0, stream, a);
+}
+// NM: rows per wave / 16; a reduction shorter than a partial-step instance's step takes kNarrow.
+template <int U, int kW, int NM, int kNarrow, int TL = XS_DOWN_TL>
+void launch_down_fmt(const FfnArgs& a, hipStream_t stream) {
+  constexpr int H = half_step(U), kStep = rest_step<kW, U>();
+  static_assert(kNarrow <= 2, "has the short case");
   const int K = a.f / a.splits;
-  if (K % (32 * U) == 0)
-    hipLaunchKernelGGL((down_kernel<U, kW, NM, false, TL>), grid, block, 0, stream, a);
-  else if (K % (32 * H) == 0)
-    hipLaunchKernelGGL((down_kernel<H, kW, NM, false, TL>), grid, block, 0, stream, a);
-  else
-    hipLaunchKernelGGL((down_kernel<rest_step<kW, U>(), kW, NM, true, TL>), grid, block, 0, stream,
-                       a);
+  if (K % (32 * U) == 0) launch_down_step<U, kW, NM, false, TL>(a, stream);
+  else if (K % (32 * H) == 0) launch_down_step<H, kW, NM, false, TL>(a, stream);
+  else if (K > 32 * kStep) launch_down_step<kStep, kW, NM, true, TL>(a, stream);
+  else launch_down_step<kStep, kW, kNarrow, true, XS_DOWN_TL>(a, stream);
 }
 
 // The persistent down launch (down_seq_kernel): one block per resident slot, rounded up to a
@@ -1728,9 +1749,9 @@ hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
     const bool wide = XS_Q4_DN_WIDE && est > 0 && (long)a.T * a.k <= 8 * est &&
                       (long)((a.d + wcols - 1) / wcols) * est * a.splits >= XS_DN_WIDE_MIN_BLOCKS;
     if (wide)
-      launch_down_fmt<XS_Q4_DOWN_U, kMx4, 2 * XS_Q4_DOWN_NM, 2>(a, stream);
+      launch_down_fmt<XS_Q4_DOWN_U, kMx4, 2 * XS_Q4_DOWN_NM, XS_Q4_DOWN_NM, 2>(a, stream);
     else
-      launch_down_fmt<XS_Q4_DOWN_U, kMx4, XS_Q4_DOWN_NM>(a, stream);
+      launch_down_fmt<XS_Q4_DOWN_U, kMx4, XS_Q4_DOWN_NM, XS_Q4_DOWN_NM>(a, stream);
     return hipGetLastError();
   }
   // bf16 and FP8: twice the rows per wave (one token load feeding twice the weight tiles)
@@ -1762,21 +1783,21 @@ hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
       if (a.splits == 1 && launch_down_seq<XS_DOWN_NM7_U, kBf16, 7>(a, stream))
         return hipGetLastError();
 #endif
-      launch_down_fmt<XS_DOWN_NM7_U, kBf16, 7>(a, stream);
+      launch_down_step<XS_DOWN_NM7_U, kBf16, 7, false, XS_DOWN_TL>(a, stream);
       return hipGetLastError();
     }
   }
 #endif
   if (a.wfmt == kFp8) {
     if (wide)
-      launch_down_fmt<XS_Q8_DOWN_U, kFp8, 2 * XS_Q8_DOWN_NM>(a, stream);
+      launch_down_fmt<XS_Q8_DOWN_U, kFp8, 2 * XS_Q8_DOWN_NM, XS_Q8_DOWN_NM>(a, stream);
     else
-      launch_down_fmt<XS_Q8_DOWN_U, kFp8, XS_Q8_DOWN_NM>(a, stream);
+      launch_down_fmt<XS_Q8_DOWN_U, kFp8, XS_Q8_DOWN_NM, XS_Q8_DOWN_NM>(a, stream);
   } else {
     if (wide)
-      launch_down_fmt<XS_DOWN_U, kBf16, 2 * XS_DOWN_NM>(a, stream);
+      launch_down_fmt<XS_DOWN_U, kBf16, 2 * XS_DOWN_NM, XS_DOWN_NM>(a, stream);
     else
-      launch_down_fmt<XS_DOWN_U, kBf16, XS_DOWN_NM>(a, stream);
+      launch_down_fmt<XS_DOWN_U, kBf16, XS_DOWN_NM, XS_DOWN_NM>(a, stream);
   }
   return hipGetLastError();
 }

@@ -85,3 +85,34 @@ def test_large_batch_shared_experts(T):
 def test_large_batch_group_share(fmt):
     RUN[fmt](dict(N=32, k=4, d=288, f=224, T=260, logits="domains", Q=5), 3, 1, 4, "per_group",
              groups=4, local=2, label=f"group share {fmt}")
+
+
+# every staged partial-step instance, after whole steps and alone, with 1 to 32 rows an expert
+# (batches of up to 32 tokens never take the large-batch launches)
+PARTIAL_DIMS = [(160, 288), (288, 160), (352, 480), (416, 352), (544, 608), (1056, 224)]
+PARTIAL_ROWS = [(9, 4, 2, 2), (16, 4, 2, 3), (24, 5, 2, 4), (32, 4, 2, 2)]     # T, N, k, M
+
+
+@FORMATS
+@pytest.mark.parametrize("d,f", PARTIAL_DIMS)
+def test_partial_steps_by_rows(fmt, d, f):
+    for T, N, k, M in PARTIAL_ROWS:
+        _case(fmt, T, N, k, d, f, M, "partial step rows")
+
+
+# one expert with more rows than a staged pass holds (32) in a batch whose others hold few, so that
+# it stays on the staged launches: a block takes its rows in two passes
+TWO_PASS_DIMS = [(352, 480), (384, 256), (544, 224), (512, 512)]
+TWO_PASS = dict(T=60, N=24, k=2, M=16)
+
+
+@FORMATS
+@pytest.mark.parametrize("d,f", TWO_PASS_DIMS)
+def test_two_staged_passes(fmt, d, f):
+    import numpy as np
+    import workloads as W
+    from helpers import oracle_route
+    cfg = dict(N=TWO_PASS["N"], k=TWO_PASS["k"], d=d, f=f, T=TWO_PASS["T"], logits="domains", Q=1)
+    ids = oracle_route(W.make_logits(cfg, 5)[0], cfg["k"], 1, TWO_PASS["M"]).ids
+    assert np.bincount(ids.ravel()).max() > 32
+    RUN[fmt](cfg, 5, 1, TWO_PASS["M"], label=f"two passes {fmt} d{d} f{f}")

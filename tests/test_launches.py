@@ -4,7 +4,8 @@ import re
 
 import pytest
 
-from launches import launches
+import test_gpu_gemm_shapes as shapes
+from launches import kernels, launches, short_names
 
 
 def route(T, N, k, **more):
@@ -87,3 +88,33 @@ def test_split_reductions_run_whole_steps(fmt):
                 assert m[2] == "true" and m[3] == "false", (c, name)
                 assert (c["d"] // grid[2]) % (32 * int(m[1])) == 0, (c, name, grid)
     assert seen > 10
+
+
+def _registers():
+    meta = kernels()
+    return dict(zip(short_names(list(meta)), meta.values()))
+
+
+def test_partial_step_instances_do_not_spill():
+    """Registers of the instances for reductions that are no multiple of the step: none in
+    scratch memory, and few enough for two waves a SIMD (bf16 with two tiles: one)."""
+    seen = 0
+    for name, k in _registers().items():
+        m = re.fullmatch(r"(gate_up|down)_kernel<(.*)>", name)
+        if m and m[2].split(", ")[4 if m[1] == "gate_up" else 3] == "true":
+            seen += 1
+            assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, (name, k)
+            assert k[".vgpr_count"] <= 256, (name, k)
+    assert seen >= 8
+
+
+@pytest.mark.parametrize("fmt", list(shapes.RUN))
+def test_partial_step_cases_run_the_partial_step(fmt):
+    """The GPU tests of the partial steps reach the instances that they are for."""
+    for names in _names([layer(T, N, k, M, d, f, fmt) for d, f in shapes.PARTIAL_DIMS
+                         for T, N, k, M in shapes.PARTIAL_ROWS]):
+        assert _instance(names, "gate_up_kernel")[4] == "true", names
+        assert _instance(names, "down_kernel")[3] == "true", names
+    for names in _names([layer(d=d, f=f, fmt=fmt, **shapes.TWO_PASS)
+                         for d, f in shapes.TWO_PASS_DIMS]):
+        assert _instance(names, "gate_up_kernel") and _instance(names, "down_kernel")
