@@ -700,14 +700,16 @@ static_assert(XS_DOWN_XCD_SLOTS >= 8, "at least one slot per XCD");
 // tokens, rows T*k + s*T + t, kSlotRows of them a slot at most; their blocks are the longest,
 // so they start first and do not trail the launch), then the routed active experts (their
 // tokens' rows in permuted order).  False for rows beyond both.  `e` is the shared or the
-// routed expert.
+// routed expert.  kW: weight format (shared experts have bf16 weights, so the others' kernels
+// carry no trace of them: the two-tile FP8 gate/up spilled two registers of its 168 with it).
 struct SlotWork {
   int e, p0, te;
   bool shared;
 };
 
+template <int kW>
 __device__ __forceinline__ bool slot_work(const FfnArgs& a, int slot, SlotWork& w) {
-  if (slot < a.shared_slots) {
+  if (kW == kBf16 && slot < a.shared_slots) {
     int t0 = 0, t1 = a.T;
     w.e = slot;
     if (a.shared_parts > 1) {
@@ -720,7 +722,7 @@ __device__ __forceinline__ bool slot_work(const FfnArgs& a, int slot, SlotWork& 
     w.shared = true;
     return true;
   }
-  const int r = slot - a.shared_slots;
+  const int r = slot - (kW == kBf16 ? a.shared_slots : 0);
   // both loads are issued together; the record is used only below the count
   const int n_active = a.counters[kCntActive];
   const int4 rec = a.active[r < a.max_active ? r : 0];
@@ -750,28 +752,29 @@ __device__ __forceinline__ const uint8_t* slot_q(const FfnArgs& a, const SlotWor
 // blocks (the launch takes two only for grids that stay large).
 // The MXFP4 one-tile instance is held to 168 registers (3 waves per SIMD): left alone the
 // compiler took 175 and 2 waves, and DeepSeek T=8 gate/up ran 14 % slower.  So are the FP8
-// instances of up to 4 words a step (XS_Q8_GU_W3).  The two-tile bf16 and FP8 instances with a
-// partial step are compiled for at most 1 and 2 waves, and then need the registers that keep
-// them there: with one wave more they ran slower (rows that start inside a cache line share it
+// instances of up to 4 words a step (XS_Q8_GU_W3) but the split two-tile one, which would spill
+// (it runs the few blocks of a launch's tail).  The two-tile bf16 and FP8 instances with a
+// partial step are compiled for at most 1 and 2 waves (the compiler then reserves the registers
+// that keep them there): with one wave more they ran slower (rows that start inside a cache line share it
 // with the next row; gate/up us at d=4128 f=2976 T=16 M=40: bf16 384 -> 408, FP8 236 -> 247).
 template <int kW, int U, int CT, bool kRest>
 constexpr int gu_max_waves() {
   if (kRest && CT == 2 && kW != kMx4) return kW == kBf16 ? 1 : 2;
   return 8;
 }
-template <int kW, int U, int CT, bool kRest>
+template <int kW, int U, int CT, bool kSplit, bool kRest>
 constexpr int gu_waves() {
   if (kW == kMx4 && CT == 1) return 3;
-  if (kW == kFp8 && U <= 4 && XS_Q8_GU_W3 && !(kRest && CT == 2)) return 3;
+  if (kW == kFp8 && U <= 4 && XS_Q8_GU_W3 && !((kSplit || kRest) && CT == 2)) return 3;
   return kRest && !(kW == kBf16 && CT == 2) ? 2 : 1;
 }
 template <int U, bool kSplit, int kW, int CT, bool kRest>
-__global__ __attribute__((amdgpu_waves_per_eu(gu_waves<kW, U, CT, kRest>(),
+__global__ __attribute__((amdgpu_waves_per_eu(gu_waves<kW, U, CT, kSplit, kRest>(),
                                               gu_max_waves<kW, U, CT, kRest>())))
 __launch_bounds__(kBlock) void gate_up_kernel(FfnArgs a) {
   constexpr int NM = 2 * CT;                   // weight tiles: W1 and W3 of each column tile
   SlotWork sw;
-  if (!slot_work(a, a.slot_base + blockIdx.y, sw)) return;
+  if (!slot_work<kW>(a, a.slot_base + blockIdx.y, sw)) return;
   XS_TIME(xs_times_gu, 2 * block_id3(), 2u * kTimeBlocks);
   const int p0 = sw.p0, te = sw.te;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -869,7 +872,7 @@ __global__ __launch_bounds__(kBlock) void gate_up_narrow_kernel(FfnArgs a) {
   using WT = WTile<kW, U>;
   constexpr int KB = 32 * U;
   SlotWork sw;
-  if (!slot_work(a, blockIdx.y, sw)) return;
+  if (!slot_work<kW>(a, blockIdx.y, sw)) return;
   XS_TIME(xs_times_gu, 2 * block_id3(), 2u * kTimeBlocks);
   const int p0 = sw.p0, te = sw.te;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -983,7 +986,7 @@ __launch_bounds__(kBlock) void down_kernel(FfnArgs a) {
     }
   }
   SlotWork sw;
-  if (!slot_work(a, slot, sw)) return;
+  if (!slot_work<kW>(a, slot, sw)) return;
   XS_TIME(xs_times_dn, 2 * block_id3(), 2u * kTimeBlocks);
   const int p0 = sw.p0, te = sw.te;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1164,7 +1167,7 @@ __launch_bounds__(kBlock) void down_seq_kernel(FfnArgs a) {
     int slot, bx;
     down_unit((int)blockIdx.x + tid * G, CB, live, xcd, slot, bx);
     SlotWork sw;
-    const bool ok = slot_work(a, slot, sw);   // slot < live: always work
+    const bool ok = slot_work<kW>(a, slot, sw);   // slot < live: always work
     s_rec[tid] = ok ? make_int4(sw.e | (sw.shared ? 1 << 30 : 0), sw.p0, sw.te, bx)
                     : make_int4(0, 0, 0, bx);
   }
@@ -1354,7 +1357,7 @@ __global__ __launch_bounds__(kBlock) void gate_up_finish_kernel(FfnArgs a) {
 // expert once; a shared expert takes every token).
 __global__ __launch_bounds__(kBlock) void gate_up_tail_finish_kernel(FfnArgs a) {
   SlotWork sw;
-  if (!slot_work(a, a.slot_base + blockIdx.y / a.T, sw)) return;
+  if (!slot_work<kBf16>(a, a.slot_base + blockIdx.y / a.T, sw)) return;
   const int t = blockIdx.y % a.T;
   if (t >= sw.te) return;
   const int c = (blockIdx.x * kBlock + threadIdx.x) * 4;

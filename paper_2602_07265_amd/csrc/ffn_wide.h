@@ -307,7 +307,7 @@ __launch_bounds__(2 * NW) void gate_up_wide_kernel(FfnArgs a) {
   SlotWork sw;
   int slot, bx;
   wide_unit(a, blockIdx.x + gridDim.x * blockIdx.y, gridDim.x, slot, bx);
-  if (!slot_work(a, slot, sw)) return;
+  if (!slot_work<kW>(a, slot, sw)) return;
   XS_TIME(xs_times_gu, 2 * block_id3(), 2u * kTimeBlocks);
   sw.e = __builtin_amdgcn_readfirstlane(sw.e);
   const int p0 = sw.p0, te = sw.te;
@@ -393,7 +393,7 @@ __launch_bounds__(2 * NW) void down_wide_kernel(FfnArgs a) {
   SlotWork sw;
   int slot, bx;
   wide_unit(a, blockIdx.x + gridDim.x * blockIdx.y, gridDim.x, slot, bx);
-  if (!slot_work(a, slot, sw)) return;
+  if (!slot_work<kW>(a, slot, sw)) return;
   XS_TIME(xs_times_dn, 2 * block_id3(), 2u * kTimeBlocks);
   sw.e = __builtin_amdgcn_readfirstlane(sw.e);
   const int p0 = sw.p0, te = sw.te;

@@ -95,17 +95,14 @@ def _registers():
     return dict(zip(short_names(list(meta)), meta.values()))
 
 
-def test_partial_step_instances_do_not_spill():
-    """Registers of the instances for reductions that are no multiple of the step: none in
-    scratch memory, and few enough for two waves a SIMD (bf16 with two tiles: one)."""
-    seen = 0
-    for name, k in _registers().items():
-        m = re.fullmatch(r"(gate_up|down)_kernel<(.*)>", name)
-        if m and m[2].split(", ")[4 if m[1] == "gate_up" else 3] == "true":
-            seen += 1
-            assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, (name, k)
-            assert k[".vgpr_count"] <= 256, (name, k)
-    assert seen >= 8
+def test_no_kernel_spills():
+    """No kernel keeps vector registers in scratch memory.  The two-tile FP8 gate/up, which is
+    held to three waves a SIMD, and the partial-step instances come closest."""
+    regs = _registers()
+    for name, k in regs.items():
+        assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, (name, k)
+    assert regs["gate_up_kernel<4, false, 1, 2, false>"][".vgpr_count"] <= 168
+    assert sum(n.endswith("true>") or "true, " in n for n in regs) >= 8
 
 
 @pytest.mark.parametrize("fmt", list(shapes.RUN))
