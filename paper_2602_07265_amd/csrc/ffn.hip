@@ -1581,9 +1581,31 @@ constexpr int half_step(int U) { return U == 8 ? 4 : U; }
 template <int kW, int U>
 constexpr int rest_step() { return kW == kMx4 ? half_step(U) : U; }
 
+// bf16 one-tile launches at odd multiples of 128: whole half steps between one and two blocks a
+// CU (there the CUs with two blocks set the time, and the half steps' three blocks would fit) of
+// experts with two rows or more.  Gate/up us at d=4992, partial step -> whole half steps: f=768
+// T=16 M=24 (288 blocks) 96 -> 89, f=1664 T=4 M=12 (312) 94 -> 89, M=16 (416) 100 -> 99; outside,
+// f=768 M=12 (144) 43 -> 57, f=1664 T=4 M=20 (520) 145 -> 157, T=32 M=40 (1040) 247 -> 260.
+template <int U>
+bool gu_half_steps(const FfnArgs& a, int K) {
+  if (K % (32 * half_step(U)) != 0 || a.est_active <= 0 || (long)a.T * a.k < 2L * a.est_active)
+    return false;
+  static std::atomic<int> cached{0};
+  const long r = resident_blocks(gate_up_kernel<U, false, kBf16, 1, true>, cached);
+  const long blocks =
+      (long)((a.f + kWaves * kCols - 1) / (kWaves * kCols)) * (a.est_active + a.shared_slots);
+  return 2 * blocks > r && blocks <= r;
+}
+
 template <int kW, int U, int CT>
 void launch_gu_step(const FfnArgs& a, int K, dim3 grid, hipStream_t stream) {
   constexpr int H = half_step(U);
+  if constexpr (kW == kBf16 && CT == 1) {
+    if (K % (32 * U) != 0 && grid.z == 1 && gu_half_steps<U>(a, K)) {
+      launch_gu<H, kW, CT, false>(a, grid, stream);
+      return;
+    }
+  }
   if (K % (32 * U) == 0)
     launch_gu<U, kW, CT, false>(a, grid, stream);
   else if (grid.z > 1 || (kW == kMx4 && K % (32 * H) == 0))
@@ -1607,6 +1629,12 @@ int down_resident() {
   return resident_blocks(down_kernel<U, kW, NM, kRest, TL>, cached);
 }
 
+// The same of the instance for reductions of K.
+template <int U, int kW, int NM>
+int down_wide_resident(int K) {
+  return K % (32 * U) == 0 ? down_resident<U, kW, NM, false>() : down_resident<U, kW, NM, true>();
+}
+
 template <int U, int kW, int NM, bool kRest, int TL>
 void launch_down_step(const FfnArgs& a, hipStream_t stream) {
   const int cols = kWaves * kCols * NM;
@@ -1614,12 +1642,30 @@ void launch_down_step(const FfnArgs& a, hipStream_t stream) {
                      dim3((a.d + cols - 1) / cols, a.max_active + a.shared_slots, a.splits),
                      dim3(kBlock), 0, stream, a);
 }
+// FP8 with 32-row waves at odd multiples of 64: whole half steps (three blocks a CU) where they
+// make one round of blocks and the partial-step instance (two) makes two.  Down us at d=2752,
+// partial step -> whole half steps: f=832 T=16 M=24 (528 blocks) 20 -> 16, f=1472 T=8 M=32 (704)
+// 37 -> 31; outside, f=1472 T=4 M=20 (440) 21 -> 23, T=16 M=40 (880) 41 -> 53.
+template <int U, int NM>
+bool down_half_steps(const FfnArgs& a, int K) {
+  if (K % (16 * U) != 0 || a.est_active <= 0) return false;
+  const int cols = kWaves * kCols * NM;
+  const long blocks = (long)((a.d + cols - 1) / cols) * a.est_active * a.splits;
+  return blocks > down_resident<U, kFp8, NM, true>() &&
+         blocks <= down_resident<U / 2, kFp8, NM, false>();
+}
 // NM: rows per wave / 16; a reduction shorter than a partial-step instance's step takes kNarrow.
 template <int U, int kW, int NM, int kNarrow, int TL = XS_DOWN_TL>
 void launch_down_fmt(const FfnArgs& a, hipStream_t stream) {
   constexpr int H = half_step(U), kStep = rest_step<kW, U>();
   static_assert(kNarrow <= 2, "has the short case");
   const int K = a.f / a.splits;
+  if constexpr (kW == kFp8 && NM == kNarrow) {
+    if (K % (32 * U) != 0 && down_half_steps<U, NM>(a, K)) {
+      launch_down_step<U / 2, kW, NM, false, TL>(a, stream);
+      return;
+    }
+  }
   if (K % (32 * U) == 0) launch_down_step<U, kW, NM, false, TL>(a, stream);
   else if (K % (32 * H) == 0) launch_down_step<H, kW, NM, false, TL>(a, stream);
   else if (K > 32 * kStep) launch_down_step<kStep, kW, NM, true, TL>(a, stream);
@@ -1768,8 +1814,8 @@ hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
   bool wide = est > 0 && (long)a.T * a.k >= XS_DN_WIDE_TOKENS * est &&
               wide_blocks >= XS_DN_WIDE_MIN_BLOCKS;
   if (!wide && est > 0 && (long)a.T * a.k >= XS_DN_WIDE_TOKENS * est) {
-    const int r = a.wfmt == kFp8 ? down_resident<XS_Q8_DOWN_U, kFp8, 2 * XS_Q8_DOWN_NM, false>()
-                                 : down_resident<XS_DOWN_U, kBf16, 2 * XS_DOWN_NM, false>();
+    const int r = a.wfmt == kFp8 ? down_wide_resident<XS_Q8_DOWN_U, kFp8, 2 * XS_Q8_DOWN_NM>(K)
+                                 : down_wide_resident<XS_DOWN_U, kBf16, 2 * XS_DOWN_NM>(K);
     wide = r > 0 && wide_blocks >= r && wide_blocks % r == 0;
   }
 #if XS_DOWN_NM7

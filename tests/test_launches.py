@@ -115,3 +115,21 @@ def test_partial_step_cases_run_the_partial_step(fmt):
     for names in _names([layer(d=d, f=f, fmt=fmt, **shapes.TWO_PASS)
                          for d, f in shapes.TWO_PASS_DIMS]):
         assert _instance(names, "gate_up_kernel") and _instance(names, "down_kernel")
+
+
+def test_whole_half_steps_by_rounds_of_blocks():
+    """bf16 gate/up at odd multiples of 128 and FP8 down at odd multiples of 64: the plain
+    instances of half the step where they make the shorter launch, and only there."""
+    case = lambda T, M, d, f, fmt: layer(T, 96, 6, M, d, f, fmt)     # noqa: E731
+    gate_up = [(case(16, 24, 4992, 768, "bf16"), "4"), (case(4, 12, 2688, 1664, "bf16"), "4"),
+               (case(32, 40, 2688, 768, "bf16"), "4"), (case(16, 12, 4992, 768, "bf16"), "8"),
+               (case(2, 12, 2688, 1664, "bf16"), "8"), (case(4, 20, 2688, 1664, "bf16"), "8"),
+               (case(32, 40, 4992, 1664, "bf16"), "8")]
+    down = [(case(16, 24, 2752, 832, "fp8"), "2"), (case(8, 32, 2752, 1472, "fp8"), "2"),
+            (case(4, 20, 2752, 1472, "fp8"), "4"), (case(16, 40, 2752, 1472, "fp8"), "4"),
+            (case(16, 24, 2752, 1440, "fp8"), "4")]
+    for kernel, rest, want in (("gate_up_kernel", 4, gate_up), ("down_kernel", 3, down)):
+        full = "8" if kernel == "gate_up_kernel" else "4"
+        for (c, step), names in zip(want, _names([c for c, _ in want])):
+            args = _instance(names, kernel)
+            assert args[0] == step and args[rest] == ("true" if step == full else "false"), (c, names)
