@@ -1497,11 +1497,11 @@ bool gu_two_tiles(const FfnArgs& a, int kW, unsigned splits) {
 // Blocks of the kernel that the GPU runs at once (0: unknown).  The callers keep the figure in
 // `cached`, one per instance (one device type; callers on several threads may fill it at once).
 template <typename K>
-int resident_blocks(K kernel, std::atomic<int>& cached) {
+int resident_blocks(K kernel, std::atomic<int>& cached, int threads = kBlock) {
   int r = cached.load(std::memory_order_relaxed);
   if (r == 0) {
     int per_cu = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess ||
         hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         per_cu <= 0)
@@ -1689,42 +1689,91 @@ bool launch_down_seq(const FfnArgs& a, hipStream_t stream) {
   return true;
 }
 
+// Gate/up with 256 weight rows a block where that leaves at least 1024 blocks (bf16) or 512 (FP8
+// and MXFP4, whose steps are twice as long then), else 128 (two blocks a CU).  Gate/up us with 256
+// / 128 rows: bf16 Mixtral T=64 (560 blocks of 256) 251 / 221, DeepSeek T=64 M=24 (384) 275 / 253,
+// T=256 M=64 (1264) 667 / 682, T=512 M=96 (2048) 1043 / 1057, Mixtral T=1024 (2577) 660 / 687; FP8
+// DeepSeek T=64 M=32 (512) 171 / 187, M=24 (384) 147 / 172, T=256 M=64 356 / 397, Qwen T=256 (384)
+// 63 / 59; MXFP4 Qwen T=256 (384) 53 / 48, Mixtral T=64 (560) 95 / 125, DeepSeek T=256 M=64 275 /
+// 353.  One GPU group's share is taken for the slots of the whole batch's rows: DeepSeek T=512 FP8
+// 115 / 93 and MXFP4 101 / 81 would run faster with 128 rows, but with its own slots at the same
+// limits others lose (d=4096 f=4096 T=512 MXFP4 249 a layer with 256, 273 with 128).
+struct WideGrid {
+  int rows;              // weight rows of a gate/up block
+  long gu, dn;           // blocks of the two launches with the slots expected
+};
+WideGrid wide_grid(const FfnArgs& a) {
+  // slots, not experts: Mixtral T=1024 has 8 experts in about 20 slots
+  const int act = a.est_active > 0 ? slot_bound(a.est_active, a.T, a.k) : a.max_active;
+  const long est = std::min(act, a.max_active) + a.shared_slots;
+  const long b256 = (long)((a.f + 127) / 128) * est * a.gu_splits;
+  const long b128 = (long)((a.f + 63) / 64) * est * a.gu_splits;
+  const bool big = b256 >= (a.wfmt == kBf16 ? 1024 : 512);
+  return {big ? 256 : 128, big ? b256 : b128, (long)((a.d + 255) / 256) * est * a.splits};
+}
+
+// A grid of more than one and fewer than `rounds` rounds of blocks whose last round is at most
+// three quarters full.
+bool short_last_round(long blocks, long resident, int rounds) {
+  if (resident <= 0 || blocks <= resident || blocks >= rounds * resident) return false;
+  const long last = blocks % resident;
+  return last != 0 && 4 * last <= 3 * resident;
+}
+template <int kW>
+bool gu_wide_short_round(const WideGrid& w, int rounds) {
+  static std::atomic<int> c256{0}, c128{0};
+  return short_last_round(w.gu, w.rows == 256
+                                    ? resident_blocks(gate_up_wide_kernel<kW, 256>, c256, 512)
+                                    : resident_blocks(gate_up_wide_kernel<kW, 128>, c128, 256),
+                          rounds);
+}
+template <int kW>
+bool dn_wide_short_round(const WideGrid& w, int rounds) {
+  static std::atomic<int> cached{0};
+  return short_last_round(w.dn, resident_blocks(down_wide_kernel<kW, 256>, cached, 512), rounds);
+}
+
 // Launches for large batches (ffn_wide.h) where an expert holds 16 rows or more on average (24
 // with MXFP4; 20 with bf16 up to 64 tokens) and the batch can give one more than 32, the rows of
-// a pass of the staged launches.  Same-box A/B, layer us against the staged launches (changes of
-// gate/up and down added): bf16 DeepSeek T=96 12 rows an expert +33 of 1009, T=128 16 rows -105
-// of 1167, T=64 21 rows -98 of 512, Qwen T=64 16 rows -4 of 90; FP8 DeepSeek T=96 12 rows -16 of
-// 572, T=64 16 rows -62 of 368, Qwen T=128 16 rows -14 of 112; MXFP4 DeepSeek T=128 16 rows +60
-// of 411, 21 rows +18 of 359, T=256 26 rows -63 of 687, Qwen T=256 32 rows -15 of 127.
+// a pass of the staged launches.  Layer us, staged -> this: bf16 DeepSeek T=96 12 rows an expert
+// 1016 -> 1048, T=128 16 rows 1176 -> 1069, Mixtral T=80 20 rows 762 -> 572; FP8 DeepSeek T=128 16
+// rows 643 -> 579, d=2048 f=1408 T=64 M=30 12.8 rows 74 -> 81 (but d=5120 f=1536 T=64 10.7 rows
+// 285 -> 267); MXFP4 DeepSeek T=128 16 rows 404 -> 463, d=5120 f=1536 T=256 26 rows 428 -> 372.
+// With few passes to save, an uneven last round of this launch's larger blocks costs more than
+// they do, and it takes more rows: FP8 19 up to 64 tokens with one to two rounds of gate/up blocks
+// (d=3072 f=1536 k=8 T=64 M=32, 1.5 rounds, 123 -> 141, T=52 M=26 110 -> 131, d=1024 f=2048 T=36
+// 16 rows 56 -> 63; at 19.6 rows 67 -> 64), MXFP4 28 below 128 tokens (Mixtral T=96 24 rows, 3.5
+// rounds, 234 -> 263, T=112 28 rows 263 -> 266; d=5120 f=1536 T=96 24 rows, 1.5 rounds, 185 ->
+// 213; d=4096 f=8192 T=64 26 rows 124 -> 136; in whole rounds T=96 24 rows 175 -> 158).
 bool wide_batch(const FfnArgs& a) {
   if (a.T <= kStageRows) return false;
   // a group's share is expected to hold its part of the routed rows
   const long rows = (long)a.T * a.k / (a.local_group >= 0 ? a.G : 1) + (long)a.n_shared * a.T;
   const long experts = (a.est_active > 0 ? a.est_active : a.max_active) + a.n_shared;
-  return rows >= (a.wfmt == kMx4 ? 24 : a.wfmt == kBf16 && a.T <= 64 ? 20 : 16) * experts;
+  long least = a.wfmt == kBf16 && a.T <= 64 ? 20 : 16;
+  if (a.wfmt == kFp8 && a.T <= 64 && gu_wide_short_round<kFp8>(wide_grid(a), 2)) least = 19;
+  if (a.wfmt == kMx4) {
+    const WideGrid w = wide_grid(a);
+    const bool uneven = gu_wide_short_round<kMx4>(w, 4) ||
+                        (a.splits == 1 && dn_wide_short_round<kMx4>(w, 2));
+    least = a.T < 128 && uneven ? 28 : 24;
+  }
+  return rows >= least * experts;
 }
 
-// Gate/up with 256 weight rows a block where that leaves at least 1024 blocks (bf16) or 512 (FP8
-// and MXFP4, whose steps are twice as long then), else 128 (two blocks a CU).  256 against 128
-// rows, layer us: bf16 Mixtral T=40 (560 blocks of 256) 427 / 390, DeepSeek T=64 M=24 (384) 476 /
-// 461, T=512 (1600) 2300 / 2317; FP8 DeepSeek T=64 M=32 (512) 331 / 348, a group share (128) 155 / 147;
-// MXFP4 Qwen T=256 (384) 128 / 121, DeepSeek T=256 M=64 (1024) 571 / 642.
 template <int kW>
 void launch_gu_wide(const FfnArgs& a, hipStream_t stream) {
   const unsigned slots = a.max_active + a.shared_slots;
-  // slots, not experts: Mixtral T=1024 has 8 experts in about 20 slots
-  const int act = a.est_active > 0 ? slot_bound(a.est_active, a.T, a.k) : a.max_active;
-  const long est = std::min(act, a.max_active) + a.shared_slots;
-  const unsigned b256 = (a.f + 127) / 128, b128 = (a.f + 63) / 64;
-  if ((long)b256 * est * a.gu_splits >= (kW == kBf16 ? 1024 : 512))
-    hipLaunchKernelGGL((gate_up_wide_kernel<kW, 256>), dim3(b256, slots, a.gu_splits), dim3(512), 0,
-                       stream, a);
+  const int rows = wide_grid(a).rows, cols = rows / 2;
+  const dim3 grid((a.f + cols - 1) / cols, slots, a.gu_splits);
+  if (rows == 256)
+    hipLaunchKernelGGL((gate_up_wide_kernel<kW, 256>), grid, dim3(512), 0, stream, a);
   else
-    hipLaunchKernelGGL((gate_up_wide_kernel<kW, 128>), dim3(b128, slots, a.gu_splits), dim3(256), 0,
-                       stream, a);
+    hipLaunchKernelGGL((gate_up_wide_kernel<kW, 128>), grid, dim3(256), 0, stream, a);
 }
-// Down always with 256 rows: with 128 DeepSeek T=256 FP8 ran 1007 us a layer against 942, Mixtral
-// T=1024 3112 against 2966, the Qwen shape at T=256 117 against 120.
+// Down always with 256 rows.  Down us with 128 / 256: DeepSeek T=256 M=64 FP8 295 / 237, T=512 FP8
+// 527 / 396, Mixtral T=1024 bf16 741 / 563, Qwen T=1024 FP8 138 / 100; the other way Qwen T=256
+// MXFP4 37 / 40, Mixtral T=64 bf16 130 / 136.
 template <int kW>
 void launch_dn_wide(const FfnArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL((down_wide_kernel<kW, 256>),
