@@ -77,18 +77,17 @@ def test_ffn_ragged_shapes():
 
 
 def test_ffn_largest_batches():
-    """The size limits: T * k = 8192 (token, slot) rows, and T = 4096 tokens; many tokens per
-    expert, so the GEMMs loop over several 32-token passes."""
+    """The size limits: T * k = 8192 (token, slot) rows, and T = 4096 tokens; hundreds of tokens
+    per expert, in slots of up to 128 of them (the large-batch launches)."""
     for T, N, k, d, f, M in [(1024, 64, 8, 64, 64, 24), (4096, 16, 2, 32, 64, 4)]:
         c = dict(N=N, k=k, d=d, f=f, T=T, logits="domains", Q=4)
         _run(c, 0, 1, M, label=f"largest T{T} k{k}")
 
 
 def test_ffn_many_rows_per_expert():
-    """Few experts holding many rows each: the GEMMs stage up to 32 token rows per pass in
-    LDS, so these cases run passes of 32 rows followed by ragged ones (1-8, 9-16, 17-24,
-    25-32 rows), with 128- and 64-element steps, a rotated down pass and blocks whose last
-    waves lie past f or d."""
+    """Few experts holding many rows each, with blocks whose last waves lie past f or d: up to 32
+    tokens in staged passes, the larger batches in the large-batch launches (staged passes of
+    more than 32 rows: test_gpu_gemm_shapes)."""
     for T, N, k, d, f, M in [(70, 8, 4, 256, 512, 4), (40, 6, 3, 384, 192, 3),
                              (20, 4, 2, 192, 320, 2), (45, 8, 2, 320, 256, 3)]:
         c = dict(N=N, k=k, d=d, f=f, T=T, logits="domains", Q=2)
@@ -122,7 +121,9 @@ def test_ffn_persistent_down_multi_pass():
     """The persistent seven-tile down launch (448 output rows per block, one block per CU)
     on experts that hold more than 32 routed rows, so a unit runs in several passes of up
     to 32 H rows, and blocks with one and with two units: N=64, k=8, T=64, d=7168 (16
-    column blocks), f=256; budgets 16 and 32 make one and two whole rounds of 256 blocks."""
+    column blocks), f=256; budget 32 makes two whole rounds of 256 blocks.  (Budget 16 holds 32
+    rows an expert on average, the large-batch launches; one round of the persistent launch:
+    test_gpu_gemm_shapes.)"""
     c = dict(N=64, k=8, d=7168, f=256, T=64, logits="domains", Q=4)
     layer = make_layer(c, 2)
     oracle = OracleOutputs(layer[2], bf16_weights_of(*layer[3:]))

@@ -69,8 +69,9 @@ def test_fp8_tiny_and_ragged():
 
 
 def test_fp8_many_rows_per_expert():
-    """Few experts holding many rows each: passes of 32 staged token rows, then ragged ones
-    (1-8, 9-16, 17-24, 25-32 rows), with blocks whose last waves lie past f or d."""
+    """Few experts holding many rows each, with blocks whose last waves lie past f or d: up to 32
+    tokens in staged passes, the larger batches in the large-batch launches (staged passes of
+    more than 32 rows: test_gpu_gemm_shapes)."""
     for T, N, k, d, f, M in [(70, 8, 4, 256, 512, 4), (40, 6, 3, 384, 192, 3),
                              (20, 4, 2, 192, 320, 2), (45, 8, 2, 320, 256, 3)]:
         _run(dict(N=N, k=k, d=d, f=f, T=T, logits="domains", Q=2), 0, 1, M,
@@ -79,7 +80,7 @@ def test_fp8_many_rows_per_expert():
 
 def test_fp8_largest_batches():
     """The size limits: T * k = 8192 (token, slot) rows, and T = 4096 tokens; experts with
-    hundreds of rows, so the GEMMs loop over many staged 32-row passes."""
+    hundreds of rows, in slots of up to 128 of them (the large-batch launches)."""
     for T, N, k, d, f, M in [(1024, 64, 8, 64, 64, 24), (4096, 16, 2, 64, 64, 4)]:
         _run(dict(N=N, k=k, d=d, f=f, T=T, logits="domains", Q=4), 0, 1, M,
              label=f"largest T{T} k{k}")

@@ -2,20 +2,23 @@
 oracle: reductions with a partial last step (and shorter than one step), under one- and
 two-tile gate/up launches and narrow and wide down launches, and the launches of large batches
 at every count of token tiles, with experts in several slots, shared experts and GPU groups."""
+import numpy as np
 import pytest
 import torch
 
 import test_gpu_ffn
 import test_gpu_fp8
 import test_gpu_mxfp4
+import workloads as W
+from helpers import oracle_route
 
 pytestmark = pytest.mark.gpu
 RUN = {"bf16": test_gpu_ffn._run, "fp8": test_gpu_fp8._run, "mxfp4": test_gpu_mxfp4._run}
 FORMATS = pytest.mark.parametrize("fmt", list(RUN))
 
 
-def _case(fmt, T, N, k, d, f, M, label):
-    RUN[fmt](dict(N=N, k=k, d=d, f=f, T=T, logits="domains", Q=3), 5, 1, M,
+def _case(fmt, T, N, k, d, f, M, label, Q=3):
+    RUN[fmt](dict(N=N, k=k, d=d, f=f, T=T, logits="domains", Q=Q), 5, 1, M,
              label=f"{label} {fmt} T{T} N{N} d{d} f{f} M{M}")
 
 
@@ -25,6 +28,8 @@ def _case(fmt, T, N, k, d, f, M, label):
 @pytest.mark.parametrize("d,f", [(32, 32), (64, 96), (96, 224), (160, 192), (224, 288),
                                  (288, 320), (352, 480), (544, 160), (480, 416)])
 def test_partial_steps(fmt, d, f):
+    # (the second batch runs the large-batch launches; test_partial_steps_by_rows has the staged
+    # ones with more rows)
     for T, N, k, M in [(5, 6, 2, 3), (41, 5, 2, 3)]:      # 1-8 rows an expert; up to 41
         _case(fmt, T, N, k, d, f, M, "partial step")
 
@@ -56,7 +61,8 @@ def test_large_batch_tiles(fmt, T, d, f):
     _case(fmt, T, 2, 2, d, f, 2, "tiles")
 
 
-# experts of 1 to 128 rows side by side; 256 weight rows a gate/up block (2048 blocks and more)
+# experts of 1 to 128 rows side by side; the first with 256 weight rows a gate/up block (2475
+# blocks), over reductions of one or two steps
 @FORMATS
 def test_large_batch_uneven_experts(fmt):
     _case(fmt, 130, 64, 16, 160, 4128, 60, "uneven")
@@ -65,7 +71,6 @@ def test_large_batch_uneven_experts(fmt):
 
 @pytest.mark.parametrize("T", [40, 129, 260])
 def test_large_batch_shared_experts(T):
-    import workloads as W
     from helpers import DEV, OracleOutputs, assert_ffn_close, bf16_weights_of, make_layer, say
     from oracle import ffn as OF
     from paper_2602_07265_amd import xshare as X
@@ -106,13 +111,63 @@ TWO_PASS_DIMS = [(352, 480), (384, 256), (544, 224), (512, 512)]
 TWO_PASS = dict(T=60, N=24, k=2, M=16)
 
 
+def _rows(T, N, k, M, Q):
+    """Routed rows of each expert of a batch that `_case` (with Q domains) runs."""
+    h = W.make_logits(dict(N=N, k=k, T=T, logits="domains", Q=Q), 5)[0]
+    return np.bincount(oracle_route(h, k, 1, M).ids.ravel(), minlength=N)
+
+
 @FORMATS
 @pytest.mark.parametrize("d,f", TWO_PASS_DIMS)
 def test_two_staged_passes(fmt, d, f):
-    import numpy as np
-    import workloads as W
-    from helpers import oracle_route
-    cfg = dict(N=TWO_PASS["N"], k=TWO_PASS["k"], d=d, f=f, T=TWO_PASS["T"], logits="domains", Q=1)
-    ids = oracle_route(W.make_logits(cfg, 5)[0], cfg["k"], 1, TWO_PASS["M"]).ids
-    assert np.bincount(ids.ravel()).max() > 32
-    RUN[fmt](cfg, 5, 1, TWO_PASS["M"], label=f"two passes {fmt} d{d} f{f}")
+    assert _rows(**TWO_PASS, Q=1).max() > 32
+    _case(fmt, *(TWO_PASS[a] for a in ("T", "N", "k")), d, f, TWO_PASS["M"], "two passes", Q=1)
+
+
+# the same with every length of the last pass (8 rows more each) and with four passes
+STAGED_PASSES = [(T, 24, 2, 16) for T in (40, 46, 60, 62)] + [(128, 40, 2, 28)]
+
+
+@FORMATS
+@pytest.mark.parametrize("T,N,k,M", STAGED_PASSES)
+def test_staged_passes_by_length(fmt, T, N, k, M):
+    rows = _rows(T, N, k, M, 1).max()
+    assert rows > (96 if T == 128 else 32)
+    _case(fmt, T, N, k, 320, 192, M, f"passes of {rows} rows", Q=1)
+
+
+# the persistent down launch with one unit a block (256 units), experts of up to 39 rows: two
+# passes a unit
+PERSISTENT = (39, 64, 8, 7168, 256, 16)                                         # T, N, k, d, f, M
+
+
+def test_persistent_down_one_round():
+    T, N, k, _, _, M = PERSISTENT
+    assert _rows(T, N, k, M, 3).max() > 32
+    _case("bf16", *PERSISTENT, "persistent down, one round")
+
+
+# large batches with 256 weight rows a gate/up block, through pairs of steps of the pipelined
+# loop, with and without a remainder, for every count of token tiles (1 to 128 rows an expert)
+WIDE_256 = dict(T=130, N=36, k=10, M=32)
+WIDE_256_DIMS = [(512, 4128), (800, 4128), (1056, 4128)]
+
+
+@FORMATS
+@pytest.mark.parametrize("d,f", WIDE_256_DIMS)
+def test_large_batch_256_rows_a_block(fmt, d, f):
+    rows = _rows(**WIDE_256, Q=3)
+    for lo, hi in ((0, 16), (16, 32), (32, 48), (48, 64), (64, 96), (96, 128)):
+        assert np.any((rows > lo) & (rows <= hi)), (lo, hi, sorted(rows))
+    _case(fmt, *(WIDE_256[a] for a in ("T", "N", "k")), d, f, WIDE_256["M"], "256 rows")
+
+
+# FP8 splits d over the waves of a block also where d is an odd multiple of 128, so that a wave's
+# part is an odd number of 32-element groups: one to five of them
+ODD_PARTS = [(1, 16, 4, 128, 96, 4), (6, 24, 2, 384, 32, 12), (16, 40, 2, 640, 160, 16),
+             (9, 20, 1, 896, 64, 9)]
+
+
+@pytest.mark.parametrize("T,N,k,d,f,M", ODD_PARTS)
+def test_waves_split_odd_d(T, N, k, d, f, M):
+    _case("fp8", T, N, k, d, f, M, "waves split odd d")

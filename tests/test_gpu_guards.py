@@ -175,6 +175,7 @@ def test_moe_guards_bf16_launch_variants():
     _moe_case("down split", _cfg(16, 8, 2, 128, 1024, 2), 0, 2)
     _moe_case("gate/up split", _cfg(16, 8, 2, 1024, 256, 2), 0, 4)
     _moe_case("many rows", _cfg(70, 8, 4, 256, 512, 2), 0, 4)
+    _moe_case("several staged passes", _cfg(72, 24, 2, 288, 224, 1), 0, 16)
 
 
 def test_moe_guards_bf16_tail_and_persistent():
@@ -183,7 +184,9 @@ def test_moe_guards_bf16_tail_and_persistent():
     more than 32 rows."""
     _moe_case("gate/up tail", _cfg(32, 16, 4, 2048, 4096, 3), 0, 9)
     torch.cuda.empty_cache()
-    _moe_case("persistent down", _cfg(64, 64, 8, 7168, 256, 4), 2, 16)
+    _moe_case("large batch, split", _cfg(64, 64, 8, 7168, 256, 4), 2, 16)
+    torch.cuda.empty_cache()
+    _moe_case("persistent down", _cfg(64, 64, 8, 7168, 256, 4), 2, 32)
     torch.cuda.empty_cache()
 
 
@@ -192,3 +195,13 @@ def test_moe_guards_low_precision():
         _moe_case("small", _cfg(16, 8, 2, 256, 512), 0, 4, fmt)
         _moe_case("ragged", _cfg(37, 24, 4, 512, 256), 1, 12, fmt)
         _moe_case("down split", _cfg(16, 8, 2, 256, 2048, 2), 0, 2, fmt)
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp8", "mxfp4"])
+def test_moe_guards_partial_steps(fmt):
+    """Reductions that end in a partial step, or are shorter than one, in the staged and in the
+    large-batch launches."""
+    _moe_case("partial step", _cfg(20, 8, 2, 352, 480), 0, 4, fmt)
+    _moe_case("short", _cfg(12, 6, 2, 96, 160), 1, 3, fmt)
+    _moe_case("several passes", _cfg(60, 24, 2, 544, 224, 1), 0, 16, fmt)
+    _moe_case("large batch", _cfg(70, 8, 4, 416, 352, 2), 0, 4, fmt)

@@ -113,7 +113,8 @@ def test_partial_step_cases_run_the_partial_step(fmt):
         assert _instance(names, "gate_up_kernel")[4] == "true", names
         assert _instance(names, "down_kernel")[3] == "true", names
     for names in _names([layer(d=d, f=f, fmt=fmt, **shapes.TWO_PASS)
-                         for d, f in shapes.TWO_PASS_DIMS]):
+                         for d, f in shapes.TWO_PASS_DIMS] +
+                        [layer(T, N, k, M, 320, 192, fmt) for T, N, k, M in shapes.STAGED_PASSES]):
         assert _instance(names, "gate_up_kernel") and _instance(names, "down_kernel")
 
 
@@ -153,3 +154,18 @@ def test_large_batch_launches_by_rounds_of_blocks():
     for case, names in zip(staged + wide, got):
         is_wide = any(n.startswith("gate_up_wide_kernel") for n in names)
         assert is_wide == (case in wide), (case, names)
+
+
+def test_large_batch_and_split_cases_run_the_kernels_they_name():
+    weight = {"bf16": "0", "fp8": "1", "mxfp4": "2"}
+    for fmt, w in weight.items():
+        for names in _names([layer(d=d, f=f, fmt=fmt, **shapes.WIDE_256)
+                             for d, f in shapes.WIDE_256_DIMS]):
+            assert _instance(names, "gate_up_wide_kernel") == [w, "256"], names
+            assert _instance(names, "down_wide_kernel") == [w, "256"], names
+    for names in _names([layer(T, N, k, M, d, f, "fp8") for T, N, k, d, f, M in shapes.ODD_PARTS]):
+        assert _instance(names, "gate_up_narrow_kernel") == ["4", "1"], names
+    # the persistent down launch of the guard test and of the multi-pass test (M = 32 of them)
+    T, N, k, d, f, M = shapes.PERSISTENT
+    for names in _names([layer(64, 64, 8, 32, 7168, 256), layer(T, N, k, M, d, f)]):
+        assert _instance(names, "down_seq_kernel") == ["4", "0", "7", "4"], names
