@@ -143,13 +143,18 @@ __device__ __forceinline__ Q4<U> load_q4(const uint8_t* p) {
     r.w[5] = w.y;
     r.w[6] = w.z;
     r.w[7] = w.w;
-  } else {
-    static_assert(U == 4, "4, 8 or 16 words");
+  } else if constexpr (U == 4) {
     const uint4 v = *reinterpret_cast<const uint4*>(p);
     r.w[0] = v.x;
     r.w[1] = v.y;
     r.w[2] = v.z;
     r.w[3] = v.w;
+  } else if constexpr (U == 2) {
+    const uint2 v = *reinterpret_cast<const uint2*>(p);
+    r.w[0] = v.x;
+    r.w[1] = v.y;
+  } else {
+    r.w[0] = *reinterpret_cast<const uint32_t*>(p);
   }
   return r;
 }
@@ -901,10 +906,7 @@ __global__ __launch_bounds__(kBlock) void gate_up_narrow_kernel(FfnArgs a) {
     const int tok = sw.shared ? p0 - a.T * (a.k + sw.e) + t : a.perm[p0 + t] / a.k;
     const uint16_t* const xr = a.x + (size_t)tok * d + kbase;
     floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
-    // a partial step of 1 to 3 groups where d is an odd multiple of 128 (FP8) or 256 (FP8, MXFP4);
-    // bf16 splits d at multiples of 256 only, whole steps of its two groups
-    constexpr bool kRest = U > 2;
-    const int Kf = kRest ? K / KB * KB : K, ut = (K - Kf) >> 5;
+    const int Kf = K / KB * KB, ut = (K - Kf) >> 5;
     typename WT::Regs b[2];
     bf16x8 x[U];
     auto load = [&](typename WT::Regs (&rb)[2], bf16x8 (&rx)[U], int k) {
@@ -913,7 +915,7 @@ __global__ __launch_bounds__(kBlock) void gate_up_narrow_kernel(FfnArgs a) {
 #pragma unroll
       for (int u = 0; u < U; ++u) rx[u] = load8(xr + k + WT::koff(g, u));
     };
-    if (!kRest || Kf > 0) load(b, x, 0);
+    if (Kf > 0) load(b, x, 0);
     for (int k = 0; k < Kf; k += KB) {
       typename WT::Regs nb[2];
       bf16x8 nx[U];
@@ -927,7 +929,7 @@ __global__ __launch_bounds__(kBlock) void gate_up_narrow_kernel(FfnArgs a) {
 #pragma unroll
       for (int u = 0; u < U; ++u) x[u] = nx[u];
     }
-    if (kRest && ut) {
+    if (ut) {                                    // the partial step
       typename WT::Rest rb[2];
 #pragma unroll
       for (int m = 0; m < 2; ++m) rb[m] = WT::load_rest(wp[m], Kf, g, 0, ut);
