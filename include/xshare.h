@@ -288,8 +288,8 @@ xshare_status xshare_select_ep(const float* logits, int32_t T, const xshare_rout
  *   stage_events: nullable; XSHARE_N_STAGE_EVENTS hipEvent_t handles created by the caller,
  *            recorded on `stream` at the stage boundaries (profiling).
  *
- * Only the weights of experts that receive at least one token are read, each once per
- * (up to) 32 tokens routed to it.  Pointers x, w1, w3, w2 and y must be 16-byte aligned.
+ * Only the weights of experts that receive at least one token are read, each once per (up to)
+ * 32 tokens routed to it, or 128 in batches that give experts many.  Pointers x, w1, w3, w2 and y must be 16-byte aligned.
  * With shared experts, y_i = sum_r w_ir * E_{e_ir}(x_i) + sum_s E^s_s(x_i), the shared
  * terms added after the routed ones.
  */
@@ -383,7 +383,8 @@ xshare_status xshare_moe_forward_v2(const xshare_layer_args* args);
  * ends.  Nothing is allocated or freed, by the library or any library it calls.
  *
  *   Arguments as xshare_moe_forward, without ws / ws_bytes.
- *   Limit: xshare_moe_workspace_bytes(T, d, f, params, ep, shared) <= the array's size
+ *   Limit: xshare_moe_workspace_bytes(T, d, f, params, ep, shared) <= the array's size (of
+ *          a batch of more than 128 tokens, up to 1024 bytes of it do not count)
  *          (for instance the DeepSeek-R1 shape, d = 7168, f = 2048, N = 256, k = 8, up to
  *          T = 64 under a total budget); larger calls return XSHARE_EWORKSPACE before
  *          anything is enqueued.

@@ -1199,12 +1199,12 @@ __global__ __launch_bounds__(kThreads) void route_kernel(RouteArgs a) {
 //                                 wave per request: its picks
 //   route_refine_kernel  (d), (e) per block the greedy, then one wave per token
 //   route_lists_kernel   (f)      per block the expert counts, then one wave per expert
-// One workgroup, where a thread per expert walked all T * k entries, took 20 times as long
-// (selection us, one workgroup -> four kernels): N=256 k=8 T=128 144 -> 22, T=512 532 -> 24;
-// N=128 T=256 267 -> 21; N=8 k=2 T=1024 343 -> 22.  What is left is four launches and the
-// latency of each one's dependent loads.  Between the kernels the plain top-k entries lie in
-// `perm` (rank << 10 | expert, -1 = none) and their gates in `w`, both overwritten with the
-// results later; an expert's score and flags in its `active` record.
+// One workgroup, where a thread per expert walked all T * k entries, took 6 to 22 times as long
+// (us a call in a stream of them, one workgroup -> four kernels): N=256 k=8 T=128 151 -> 26, T=512
+// 585 -> 35, T=1024 1157 -> 52; N=128 T=256 287 -> 27; N=8 k=2 T=1024 353 -> 27.  What is left is
+// four launches and the latency of each one's dependent loads.  Between the kernels the plain
+// top-k entries lie in `perm` (rank << 10 | expert, -1 = none) and their gates in `w`, both
+// overwritten with the results later; an expert's score and flags in its `active` record.
 constexpr int kTokThreads = 256;
 constexpr int kTokWaves = kTokThreads / 64;
 constexpr uint32_t kFlagU = 1, kFlagS0 = 2;
