@@ -41,6 +41,24 @@ def test_partial_steps_wide_launches(fmt):
     _case(fmt, 40, 120, 16, 1760, 160, 110, "wide down")
 
 
+# whole half steps (format, T, N, k, d, f, M; kernel and its instance): bf16 gate/up with 257 to
+# 512 blocks, FP8 down with 513 to 768, MXFP4 at odd multiples of 128 in two-tile gate/up and
+# 64-row down waves; and 64-row down waves whose reduction is shorter than a step, which take the
+# 32-row instance
+HALF_STEPS = [("bf16", 12, 40, 8, 384, 512, 34, "gate_up_kernel<4, false, 0, 1, false>"),
+              ("fp8", 12, 48, 8, 1664, 192, 40, "down_kernel<2, 1, 2, false, 4>"),
+              ("mxfp4", 40, 120, 16, 384, 928, 110, "gate_up_kernel<4, false, 2, 2, false>"),
+              ("mxfp4", 40, 120, 16, 1760, 384, 110, "down_kernel<4, 2, 4, false, 2>"),
+              ("fp8", 40, 120, 16, 1760, 96, 110, "down_kernel<4, 1, 2, true, 4>"),
+              ("mxfp4", 40, 120, 16, 1760, 96, 110, "down_kernel<4, 2, 2, true, 4>"),
+              ("bf16", 40, 120, 16, 1760, 32, 110, "down_kernel<2, 0, 2, true, 4>")]
+
+
+@pytest.mark.parametrize("fmt,T,N,k,d,f,M,kernel", HALF_STEPS)
+def test_half_steps_and_short_reductions(fmt, T, N, k, d, f, M, kernel):
+    _case(fmt, T, N, k, d, f, M, kernel)
+
+
 # few small experts with a few rows each: the waves of a gate/up block split d (in 64 to 576
 # elements a wave, whole steps and partial ones)
 @FORMATS

@@ -157,6 +157,9 @@ def test_large_batch_launches_by_rounds_of_blocks():
 
 
 def test_large_batch_and_split_cases_run_the_kernels_they_name():
+    cases = [layer(T, N, k, M, d, f, fmt) for fmt, T, N, k, d, f, M, _ in shapes.HALF_STEPS]
+    for case, names in zip(shapes.HALF_STEPS, _names(cases)):
+        assert case[-1] in names, (case, names)
     weight = {"bf16": "0", "fp8": "1", "mxfp4": "2"}
     for fmt, w in weight.items():
         for names in _names([layer(d=d, f=f, fmt=fmt, **shapes.WIDE_256)
